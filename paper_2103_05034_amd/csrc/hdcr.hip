@@ -10,10 +10,7 @@
 //   neighbours only, and is stored as that 9-point stencil, [nb][9][n][n]
 //   complex with entry (j, k) at k * n + j: stencil point d < 8 is the block
 //   that the hop direction d (2 mu + 0 forward, + 1 backward) leads to, point 8
-//   the block itself.  It is built one basis vector k at a time: one kernel
-//   writes the nine fields F_d = Gamma_5 (-1/2) D_hop^{(d), across a block face}
-//   phi_k and F_8 = Gamma_5 (M5D - 1/2 D_hop^{(inside the block)}) phi_k, whose
-//   restrictions onto the basis are column k of every stencil matrix.
+//   the block itself.  stencil.hip builds it in one launch.
 // * Smoother S_cheb([a,b],N) (Chebyshev smoothers section) with M = H_DW:
 //   [c_0/2 + sum c_j T_j(x(D^dag D))] H_DW r by Clenshaw's recurrence, each
 //   step D_DW then D_DW^dag with the recurrence fused into the last hop pass.
@@ -57,154 +54,6 @@ __global__ void __launch_bounds__(CB) g5_combine_kernel(long long nsite, int Ls,
     o.y += w.y;
   }
   out[i] = o;
-}
-
-// One hop direction D at a site of the out parity: acc = (1 -+ g_mu) U psi
-// (non-adjoint D_hop), the link read from the packed [D][9][V4h] table.
-template <int D>
-__device__ __forceinline__ void dir_term(const double2* __restrict__ lk, long long V4h, const cplx<double> psi[12],
-                                         cplx<double> acc[12]) {
-  constexpr int MU = D / 2;
-  constexpr int SIGMA = (D % 2) ? +1 : -1;
-  cplx<double> hs[6], chi[6];
-  project<MU, SIGMA>(psi, hs);
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    const double2 u0 = lk[(size_t)(3 * i + 0) * V4h], u1 = lk[(size_t)(3 * i + 1) * V4h],
-                  u2 = lk[(size_t)(3 * i + 2) * V4h];
-#pragma unroll
-    for (int sp = 0; sp < 2; ++sp) {
-      cplx<double> v = cmul(cplx<double>{u0.x, u0.y}, hs[3 * sp + 0]);
-      v = cfma(cplx<double>{u1.x, u1.y}, hs[3 * sp + 1], v);
-      v = cfma(cplx<double>{u2.x, u2.y}, hs[3 * sp + 2], v);
-      chi[3 * sp + i] = v;
-    }
-  }
-#pragma unroll
-  for (int c = 0; c < 12; ++c) acc[c] = {0, 0};
-  reconstruct<MU, SIGMA>(chi, acc);
-}
-
-struct CoarsenArgs {
-  Geom g;
-  int blk[4];
-  double d, mf;                // 5 - M5, mass
-  const double2* links;        // [2][8][9][V4h]
-  const int* nbr;              // [2][8][V4h]
-  const char* phi_e;           // basis vector, even half
-  const char* phi_o;           // odd half
-  char* out;                   // 9 fields, both layout: even halves of F_0..F_8, then the odd halves
-  size_t fb;                   // bytes of a half field
-};
-
-template <int D>
-__device__ __forceinline__ void coarsen_dir(const CoarsenArgs& a, int p, long long h, int s_src, const int c[4],
-                                            const int ext[4], cplx<double> inside[12], cplx<double> face[12],
-                                            bool& is_face) {
-  constexpr int MU = D / 2;
-  const long long V4h = a.g.V4h;
-  const int nh = a.nbr[((size_t)p * 8 + D) * V4h + h];
-  const char* src = p ? a.phi_e : a.phi_o;  // neighbours live on the other parity
-  cplx<double> psi[12], t[12];
-  Store<DWF_F64>::load(src, V4h, a.g.Ls, nh, s_src, psi);
-  dir_term<D>(reinterpret_cast<const double2*>(a.links) + ((size_t)(p * 8 + D) * 9) * V4h + h, V4h, psi, t);
-  const int cn = (D % 2) ? (c[MU] + ext[MU] - 1) % ext[MU] : (c[MU] + 1) % ext[MU];
-  is_face = cn / a.blk[MU] != c[MU] / a.blk[MU];
-#pragma unroll
-  for (int k = 0; k < 12; ++k) {
-    face[k] = is_face ? t[k] : cplx<double>{0, 0};
-    if (!is_face) inside[k] = cadd(inside[k], t[k]);
-  }
-}
-
-// Thread per (parity, half-lattice site, s).  F_r at slice s takes the terms at
-// the mirrored slice Ls-1-s (the reflection in Gamma_5), times gamma_5.
-__global__ void __launch_bounds__(CB) coarsen_kernel(CoarsenArgs a) {
-  const long long V4h = a.g.V4h;
-  const int Ls = a.g.Ls;
-  const long long i = (long long)blockIdx.x * CB + threadIdx.x;
-  if (i >= 2 * V4h * Ls) return;
-  const int p = (int)(i / (V4h * Ls));
-  const long long rem = i - (long long)p * V4h * Ls;
-  const long long h = rem / Ls;
-  const int s = (int)(rem - h * Ls);
-  const int sr = Ls - 1 - s;
-  int c[4];
-  site_coords(a.g, p, h, c[0], c[1], c[2], c[3]);
-  const int ext[4] = {a.g.X, a.g.Y, a.g.Z, a.g.T};
-  cplx<double> inside[12], face[12];
-#pragma unroll
-  for (int k = 0; k < 12; ++k) inside[k] = {0, 0};
-  bool f;
-  auto emit = [&](int r) {
-    cplx<double> o[12];
-#pragma unroll
-    for (int k = 0; k < 12; ++k) {
-      const double sg = k < 6 ? -0.5 : 0.5;  // Gamma_5 (-1/2)
-      o[k] = {sg * face[k].re, sg * face[k].im};
-    }
-    Store<DWF_F64>::store(a.out + ((size_t)p * 9 + r) * a.fb, V4h, Ls, h, s, o);
-  };
-  coarsen_dir<0>(a, p, h, sr, c, ext, inside, face, f);
-  emit(0);
-  coarsen_dir<1>(a, p, h, sr, c, ext, inside, face, f);
-  emit(1);
-  coarsen_dir<2>(a, p, h, sr, c, ext, inside, face, f);
-  emit(2);
-  coarsen_dir<3>(a, p, h, sr, c, ext, inside, face, f);
-  emit(3);
-  coarsen_dir<4>(a, p, h, sr, c, ext, inside, face, f);
-  emit(4);
-  coarsen_dir<5>(a, p, h, sr, c, ext, inside, face, f);
-  emit(5);
-  coarsen_dir<6>(a, p, h, sr, c, ext, inside, face, f);
-  emit(6);
-  coarsen_dir<7>(a, p, h, sr, c, ext, inside, face, f);
-  emit(7);
-  // M5D at the mirrored slice: (5 - M5) v_s - P_- v_{s+1} - P_+ v_{s-1}, the
-  // ends wrapping round with +mf instead of -1
-  const char* self = p ? a.phi_o : a.phi_e;
-  cplx<double> v0[12], vu[12], vd[12];
-  Store<DWF_F64>::load(self, V4h, Ls, h, sr, v0);
-  const int su = sr + 1 < Ls ? sr + 1 : 0, sd = sr > 0 ? sr - 1 : Ls - 1;
-  const double cu = sr + 1 < Ls ? -1.0 : a.mf, cd = sr > 0 ? -1.0 : a.mf;
-  Store<DWF_F64>::load(self, V4h, Ls, h, su, vu);
-  Store<DWF_F64>::load(self, V4h, Ls, h, sd, vd);
-  cplx<double> o[12];
-#pragma unroll
-  for (int k = 0; k < 12; ++k) {
-    cplx<double> m = {a.d * v0[k].re, a.d * v0[k].im};
-    if (k < 6) {  // P_+ (upper spins) from below
-      m.re += cd * vd[k].re;
-      m.im += cd * vd[k].im;
-    } else {  // P_- (lower spins) from above
-      m.re += cu * vu[k].re;
-      m.im += cu * vu[k].im;
-    }
-    m.re -= 0.5 * inside[k].re;
-    m.im -= 0.5 * inside[k].im;
-    const double sg = k < 6 ? 1.0 : -1.0;
-    o[k] = {sg * m.re, sg * m.im};
-  }
-  Store<DWF_F64>::store(a.out + ((size_t)p * 9 + 8) * a.fb, V4h, Ls, h, s, o);
-}
-
-// Stencil storage: complex128, or complex64 (the coarse solve's tolerance of a
-// few per cent does not need FP64 matrix entries; vectors and sums stay FP64).
-__device__ __forceinline__ void put(double2* p, double2 v) { *p = v; }
-__device__ __forceinline__ void put(float2* p, double2 v) { *p = make_float2((float)v.x, (float)v.y); }
-
-// A[b][r][k][j] = coef[r][b][j] for basis vector k.
-template <class T>
-__global__ void __launch_bounds__(CB) coarse_scatter_kernel(const double2* __restrict__ coef, T* __restrict__ A,
-                                                            int nb, int n, int k) {
-  const long long i = (long long)blockIdx.x * CB + threadIdx.x;
-  if (i >= (long long)9 * nb * n) return;
-  const int j = (int)(i % n);
-  const long long rb = i / n;
-  const int b = (int)(rb % nb);
-  const int r = (int)(rb / nb);
-  put(&A[(((size_t)b * 9 + r) * n + k) * n + j], coef[i]);
 }
 
 // y[b] = sum_r A[b][r] x[neighbour_r(b)]: one workgroup per block, lane j
@@ -389,7 +238,6 @@ struct dwf_hdcr_s {
   dwf_hdcr_params prm;
   const char* basis;   // caller's basis (packed both layout, nvec fields), set by dwf_hdcr_set_basis
   void* A;             // [nb][9][n][n], complex128 or complex64 (prm.coarse_prec)
-  double2* coef;       // [9][nb][n]
   double2* cv[7];      // coarse vectors: d, c, r, p, q, w, b'
   double* part;        // [2][CRED] partials, 2 result doubles, then the coarse CG's CS_N scalars
   char* work;          // 9 both fields
@@ -429,7 +277,6 @@ size_t carve_hdcr(dwf_hdcr_s* d, const dwf_context* h, int nvec, int nk, char* b
   dwf_hdcr_s tmp;
   dwf_hdcr_s* x = d ? d : &tmp;
   x->A = take((size_t)h->nb * 9 * nvec * nvec * 16);  // sized for complex128
-  x->coef = reinterpret_cast<double2*>(take(9 * cvb));
   for (int i = 0; i < 7; ++i) x->cv[i] = reinterpret_cast<double2*>(take(cvb));
   x->part = reinterpret_cast<double*>(take((2 * CRED + 2 + CS_N) * sizeof(double)));
   x->work = take(9 * 2 * fb);
@@ -779,33 +626,7 @@ int dwf_hdcr_set_basis(dwf_hdcr hd, const void* basis) {
   if (!basis) return fail(DWF_EINVAL, "dwf_hdcr_set_basis: basis is NULL");
   dwf_context* c = hd->h;
   hd->basis = reinterpret_cast<const char*>(basis);
-  const int n = hd->nvec;
-  CoarsenArgs a{};
-  a.g = c->g;
-  for (int i = 0; i < 4; ++i) a.blk[i] = c->blk[i];
-  a.d = 5.0 - c->M5;
-  a.mf = c->mf;
-  a.links = reinterpret_cast<const double2*>(c->links64);
-  a.nbr = c->nbr;
-  a.out = hd->work;
-  a.fb = hd->fb;
-  const long long threads = 2 * c->g.V4h * c->g.Ls;
-  for (int k = 0; k < n; ++k) {
-    a.phi_e = hd->basis + (size_t)k * hd->fb;
-    a.phi_o = hd->basis + (size_t)(n + k) * hd->fb;
-    hipLaunchKernelGGL(coarsen_kernel, dim3(blocks_for(threads)), dim3(CB), 0, c->stream, a);
-    HIP_TRY(hipGetLastError());
-    // the nine fields as a both-layout array of 9 rhs: restrict all of them
-    HIP_TRY(launch_block_dot(c, DWF_F64, hd->basis, n, hd->work, 9, reinterpret_cast<double*>(hd->coef), false));
-    const long long m = (long long)9 * hd->nb * n;
-    if (hd->prm.coarse_prec == DWF_F32)
-      hipLaunchKernelGGL(coarse_scatter_kernel<float2>, dim3(blocks_for(m)), dim3(CB), 0, c->stream, hd->coef,
-                         reinterpret_cast<float2*>(hd->A), hd->nb, n, k);
-    else
-      hipLaunchKernelGGL(coarse_scatter_kernel<double2>, dim3(blocks_for(m)), dim3(CB), 0, c->stream, hd->coef,
-                         reinterpret_cast<double2*>(hd->A), hd->nb, n, k);
-    HIP_TRY(hipGetLastError());
-  }
+  HIP_TRY(launch_stencil(c, hd->basis, hd->nvec, hd->prm.coarse_prec, hd->A));
   return sync(c);
 }
 

@@ -141,6 +141,10 @@ hipError_t launch_block_gram(dwf_context* c, int prec, const char* basis, int nv
 // per block: Cholesky of the Gram matrix ([b][k][j] = <phi_j, phi_k>) and W = R^{-1}
 hipError_t launch_block_cholesky(dwf_context* c, const double* gram, double* w, int nvec, int* flag);
 
+// stencil.hip: the little Dirac operator [nb][9][nvec][nvec] of H_DW on a blocked basis (fields of
+// both parities, FP64), stored as complex128 or complex64 (prec DWF_F32)
+hipError_t launch_stencil(dwf_context* c, const char* basis, int nvec, int prec, void* A);
+
 // force.hip
 hipError_t launch_force(dwf_context* ctx, const char* a_even, const char* a_odd, const char* b_even,
                         const char* b_odd, double* grad_U);

@@ -354,3 +354,38 @@ def test_fullsize_algorithm_b_stencil_on_patches():
                 # <phi_j^a | H | phi_k^b> is point d of block a
                 assert np.max(np.abs(col[a_patch] - Sh[a_full, d, k])) < 1e-12 * scale
     hd.close()
+
+
+@pytest.mark.parametrize(
+    "dims, Ls, block, nvec",
+    [
+        ((4, 4, 4, 4), 4, (2, 2, 2, 2), 1),  # one vector in a tile of 16
+        ((4, 4, 4, 8), 5, (2, 2, 2, 4), 16),  # a full tile; Ls no multiple of the 4 slices of a step
+        ((4, 8, 4, 4), 3, (4, 2, 2, 2), 17),  # one vector into the second tile; one block along x: no faces there
+        ((4, 4, 2, 4), 6, (2, 2, 1, 2), 33),  # third tile; blocks one site thick
+        ((4, 4, 4, 2), 2, (2, 2, 2, 2), 48),  # three full tiles; one block along t
+        ((4, 4, 4, 4), 1, (4, 2, 4, 2), 49),  # four tiles in groups of two by two, the last one nearly empty
+        ((4, 4, 2, 2), 4, (2, 2, 2, 2), 64),  # the most vectors
+    ],
+)
+def test_stencil_shapes_match_oracle(dims, Ls, block, nvec):
+    """The little Dirac operator of arbitrary (Gaussian) fields, entry by entry."""
+    import paper_2103_05034_amd as dwf
+
+    op, U = make_operator(dims, Ls, prec=F64, max_nrhs=1, max_cg_rhs=2)
+    op.set_blocks(block, both=True)
+    V = synth.gaussian_fermion_batch(dims, Ls, nvec, 41)
+    basis = pack(op, V, BOTH)
+    want = H.coarse_operator(lambda v: L.hdw(U, v, M5, MF), list(V), dims, block)
+    # an entry sums K products of values that carry a few roundings each: |error| <= (K + 100) u |phi_j^b| |H phi_k|
+    # with |H| <= 5 - M5 + 1 + 8 (the links are unitary)
+    K = 12 * Ls * int(np.prod(block))
+    norm = max(float(np.linalg.norm(v)) for v in V)
+    tol = (K + 100) * 2.0**-53 * norm * norm * 13.0
+    hd = dwf.HDCR(op, nvec, nkrylov=1)
+    hd.set_basis(basis)
+    S = host(hd.coarse_operator())
+    assert np.all(np.abs(dense_from_stencil(S, dims, block) - want) <= tol)
+    hd32 = dwf.HDCR(op, nvec, nkrylov=1, coarse_prec=1)
+    hd32.set_basis(basis)
+    assert np.array_equal(host(hd32.coarse_operator()), S.astype(np.complex64))  # the same sums, rounded once
