@@ -3,13 +3,16 @@
 // the 9-point stencil [nb][9][n][n] with entry (j, k) at k * n + j (points as in
 // dwf_hdcr_coarse_data).
 //
-// One workgroup forms one stencil point of one block as a matrix product over the
-// block's 5D sites: rows j, columns k, in 16 x 16 tiles of the FP64 matrix cores.
-// The operands come straight from the fields.  A lane holds one vector and one
-// slice (16 vectors x 4 slices per wave), so it loads whole spinors, projects and
-// rotates them in its registers, and every spin-colour component is then one
-// step of the product's inner index; nothing is staged and no intermediate
-// field is written.
+// One workgroup owns a block.  Its waves are four directions times KW tiles of 16
+// columns k; every wave keeps the 16 x 16 tiles of the FP64 matrix cores of its
+// direction's face and of its part of the block itself, for JT tiles of rows j.
+// The workgroup walks the block's sites, eight slices (a 128-byte line of FP64
+// spinors) at a time: the site's own vectors phi_j pass through LDS, where all
+// waves read them as left operands, and each wave loads the neighbour's spinors
+// phi_k straight into registers, projects and rotates them there and uses them as
+// right operands.  Every spin-colour component is then one step of the product's
+// inner index; no intermediate field is written, and every line of the basis that
+// is fetched is used whole.
 //
 // Two identities keep the work small.  Across a face the hop needs only half
 // spinors: phi_j^dag gamma_5 (1 + sigma g_mu) chi = (u_j - sigma B l_j)^dag (u + sigma B l)_chi,
@@ -17,13 +20,14 @@
 // points are the conjugate transposes of the neighbouring blocks' forward ones:
 // four face products and one for the block itself instead of nine.
 //
-// What bounds it: the fabric.  16^3 x 32, Ls 16, 32 vectors on 2^4 blocks is 0.41
-// TFLOP (24 complex inner steps per 5D site, 6 ms of matrix core time) and takes
-// 41.9 ms: the vectors of a workgroup's loads are 64-byte pieces of 128-byte lines
-// that are gone from L1 and L2 when their other half is wanted, 2.2e9 line reads
-// (285 GB, 6.3 TB/s) where 13 GB of basis are needed.  The form before this one
-// wrote nine fields per basis vector and restricted each onto the whole basis,
-// which read the basis five times per vector: 392 ms.
+// What bounds it: the fabric, then the matrix cores.  16^3 x 32, Ls 16, 32 vectors on
+// 2^4 blocks takes 21.5 ms: 0.62 TFLOP (36 complex inner steps per 5D site, 9 ms at the
+// 69 TFLOP/s the FP64 matrix cores reach) and 108 GB of line reads at 5.0 TB/s -- own
+// vectors once, neighbours four times, the site-local part twice; a block's 1.6 MB of
+// vectors do not stay in an L2 that 32 workgroups share.  Measured before: a workgroup
+// per stencil point and block with both operands loaded 64 bytes of a line at a time,
+// 41.9 ms (285 GB, 6.3 TB/s); nine fields written per basis vector and each restricted
+// onto the whole basis, 389 ms.
 #include "dwf_internal.hpp"
 #include "kernels.hpp"
 
@@ -32,17 +36,13 @@ namespace {
 
 typedef double d4v __attribute__((ext_vector_type(4)));
 
-constexpr int WAVES = 4;  // waves of a workgroup; each takes every fourth site of the block
+constexpr int SL = 8;  // slices of a step: one 128-byte line of an FP64 component
 
 struct StencilArgs {
   Geom g;
   int blk[4];
   int nsb, nb, nb8, n;
-  int groups;           // tile groups along each of j and k
   double d, mf;         // 5 - M5, mass
-  const double2* links; // [2][8][9][V4h]
-  const int* nbr;       // [2][8][V4h]
-  const int* bsite;     // [nb][nsb], odd sites as h + V4h
   const int* bnbr;      // [nb][8]
   const char* basis;    // n fields of both parities: even halves, then odd halves
   size_t fb;            // bytes of a half field
@@ -56,268 +56,303 @@ __device__ __forceinline__ void tile_step(cplx<double> a, cplx<double> b, d4v& r
   im = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.im, b.re, im, 0, 0, 0);
 }
 
-// chi = U (1 + sigma g_mu)-half of psi; the link is the same for the whole wave
-template <int D>
-__device__ __forceinline__ void rotated_half(const double2* __restrict__ lk, long long V4h, const cplx<double> psi[12],
-                                             cplx<double> chi[6]) {
-  constexpr int MU = D / 2;
-  constexpr int SIGMA = (D % 2) ? +1 : -1;
-  cplx<double> hs[6];
-  project<MU, SIGMA>(psi, hs);
+// A wave's direction mu is a run-time value: one code path for the four directions.
+// Upper half of (1 + sigma g_mu) psi = u + sigma B_mu l: for upper spin sp, B_mu takes the
+// lower spin whose first component is lo[sp], times cr[sp] + i ci[sp], one of the two being
+// zero (so the fmas below round once, as an add).
+struct Direction {
+  int mu, lo[2];
+  double cr[2], ci[2];
+  __device__ __forceinline__ explicit Direction(int m) : mu(m) {
+    lo[0] = m < 2 ? 9 : 6;
+    lo[1] = m < 2 ? 6 : 9;
+    cr[0] = m == 1 ? -1.0 : (m == 3 ? 1.0 : 0.0);
+    cr[1] = m == 1 || m == 3 ? 1.0 : 0.0;
+    ci[0] = m == 0 || m == 2 ? 1.0 : 0.0;
+    ci[1] = m == 0 ? 1.0 : (m == 2 ? -1.0 : 0.0);
+  }
+  template <int SIGMA>
+  __device__ __forceinline__ cplx<double> half(int sp, double2 u, double2 l) const {
+    const double r = SIGMA * cr[sp], i = SIGMA * ci[sp];
+    return {fma(r, l.x, fma(-i, l.y, u.x)), fma(r, l.y, fma(i, l.x, u.y))};
+  }
+};
+
+// Spin sp of the forward hop at one site, for the two slices of this lane: chi = U
+// (1 - g_mu)-half of phi_k (ul: the spinors' two components per colour).  The link is the
+// same for the whole wave.
+__device__ __forceinline__ void rotate_spin(const Direction& d, int sp, const double2* __restrict__ lk, long long V4h,
+                                            const double2 (&ul)[2][2][3], const bool (&in)[2],
+                                            cplx<double> (&chi)[2][3]) {
 #pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    const double2 u0 = lk[(size_t)(3 * i + 0) * V4h], u1 = lk[(size_t)(3 * i + 1) * V4h],
-                  u2 = lk[(size_t)(3 * i + 2) * V4h];
+  for (int hf = 0; hf < 2; ++hf) {
+    cplx<double> hs[3];
 #pragma unroll
-    for (int sp = 0; sp < 2; ++sp) {
-      cplx<double> v = cmul(cplx<double>{u0.x, u0.y}, hs[3 * sp + 0]);
-      v = cfma(cplx<double>{u1.x, u1.y}, hs[3 * sp + 1], v);
-      v = cfma(cplx<double>{u2.x, u2.y}, hs[3 * sp + 2], v);
-      chi[3 * sp + i] = v;
+    for (int c = 0; c < 3; ++c) hs[c] = d.half<-1>(sp, ul[hf][0][c], ul[hf][1][c]);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const double2 u0 = lk[(3 * i + 0) * V4h], u1 = lk[(3 * i + 1) * V4h], u2 = lk[(3 * i + 2) * V4h];
+      cplx<double> v = cmul(cplx<double>{u0.x, u0.y}, hs[0]);
+      v = cfma(cplx<double>{u1.x, u1.y}, hs[1], v);
+      v = cfma(cplx<double>{u2.x, u2.y}, hs[2], v);
+      chi[hf][i] = in[hf] ? v : cplx<double>{0, 0};  // Ls no multiple of SL: idle slices count as zero
     }
   }
 }
 
-// Component 3 sp + a of (1 + g_mu) psi's upper half, u + B_mu l, from u = component
-// 3 sp + a and the lower component that B_mu pairs with it (project<MU, +1> one
-// component at a time).
-template <int MU>
-__device__ __forceinline__ constexpr int lower_of(int c6) {
-  return MU < 2 ? (c6 < 3 ? 9 + c6 : 3 + c6) : 6 + c6;
-}
-template <int MU>
-__device__ __forceinline__ cplx<double> project_one(double2 u, double2 l, int c6) {
-  const bool first = c6 < 3;
-  if (MU == 0) return {u.x - l.y, u.y + l.x};                                                  // (i l1, i l0)
-  if (MU == 1) return first ? cplx<double>{u.x - l.x, u.y - l.y} : cplx<double>{u.x + l.x, u.y + l.y};  // (-l1, l0)
-  if (MU == 2) return first ? cplx<double>{u.x - l.y, u.y + l.x} : cplx<double>{u.x + l.y, u.y - l.x};  // (i l0, -i l1)
-  return {u.x + l.x, u.y + l.y};                                                               // (l0, l1)
-}
-
-// Does hop direction D lead from coordinate c out of its block?
-template <int D>
-__device__ __forceinline__ bool leaves_block(const StencilArgs& a, const int c[4]) {
-  constexpr int MU = D / 2;
-  const int ext[4] = {a.g.X, a.g.Y, a.g.Z, a.g.T};
-  const int cn = (D % 2) ? (c[MU] + ext[MU] - 1) % ext[MU] : (c[MU] + 1) % ext[MU];
-  return cn / a.blk[MU] != c[MU] / a.blk[MU];
-}
-
-// Wave-uniform site i of block b: its half-lattice index, parity and coordinates.
-__device__ __forceinline__ void block_site(const StencilArgs& a, int b, int i, long long& h, int& p, int c[4]) {
-  long long e = __builtin_amdgcn_readfirstlane(a.bsite[(size_t)b * a.nsb + i]);
-  p = e >= a.g.V4h ? 1 : 0;
-  h = e - p * a.g.V4h;
-  site_coords(a.g, p, h, c[0], c[1], c[2], c[3]);
-}
-
-__device__ __forceinline__ const char* half_of(const StencilArgs& a, int vec, int p) {
-  return a.basis + ((size_t)p * a.n + vec) * a.fb;
-}
-
-// Forward face in direction MU: sum over the sites whose hop leaves the block of
-// conj((1 + g_mu)-half of phi_j(x, s)) U (1 - g_mu)-half of phi_k(x + mu, Ls-1-s).
-template <int MU, int T>
-__device__ __forceinline__ void face_product(const StencilArgs& a, int b, const int (&vj)[T], const int (&vk)[T],
-                                             d4v (&re)[T][T], d4v (&im)[T][T]) {
-  const int q = (threadIdx.x & 63) >> 4;
-  const int Ls = a.g.Ls;
-  const long long V4h = a.g.V4h;
-  for (int i = threadIdx.x >> 6; i < a.nsb; i += WAVES) {
-    long long h;
-    int p, c[4];
-    block_site(a, b, __builtin_amdgcn_readfirstlane(i), h, p, c);
-    if (!leaves_block<2 * MU>(a, c)) continue;
-    const long long nh = __builtin_amdgcn_readfirstlane(a.nbr[((size_t)p * 8 + 2 * MU) * V4h + h]);
-    const double2* lk = a.links + ((size_t)(p * 8 + 2 * MU) * 9) * V4h + h;
-    for (int s0 = 0; s0 < Ls; s0 += 4) {
-      const bool in = s0 + q < Ls;  // Ls not a multiple of four: the last step's idle slices count as zero
-      const int s = in ? s0 + q : Ls - 1;
-      cplx<double> hk[T][6];
+// acc += conj((1 + g_mu)-half of phi_j) chi, phi_j from LDS ([12][SL][stride], this lane's
+// slice and vector at own)
+template <int JT>
+__device__ __forceinline__ void hop_steps(const Direction& d, int sp, const double2* own, int stride,
+                                          const cplx<double> (&chi)[2][3], d4v (&re)[JT], d4v (&im)[JT]) {
+  const double2* up = own + 3 * sp * SL * stride;
+  const double2* lo = own + d.lo[sp] * SL * stride;
 #pragma unroll
-      for (int t = 0; t < T; ++t) {
-        cplx<double> psi[12];
-        Store<DWF_F64>::load(half_of(a, vk[t], 1 - p), V4h, Ls, nh, Ls - 1 - s, psi);
-        rotated_half<2 * MU>(lk, V4h, psi, hk[t]);
+  for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+      for (int t = 0; t < JT; ++t) {
+        const int o = (c * SL + 4 * hf) * stride + 16 * t;
+        tile_step(d.half<+1>(sp, up[o], lo[o]), chi[hf][c], re[t], im[t]);
       }
-      const double2* pj[T];  // phi_j is read as its components are needed: holding it would cost a wave per SIMD
-#pragma unroll
-      for (int t = 0; t < T; ++t)
-        pj[t] = reinterpret_cast<const double2*>(half_of(a, vj[t], p)) + h * 12 * Ls + s;
-#pragma unroll
-      for (int c6 = 0; c6 < 6; ++c6) {
-#pragma unroll
-        for (int t = 0; t < T; ++t)
-          if (!in) hk[t][c6] = {0, 0};
-#pragma unroll
-        for (int tj = 0; tj < T; ++tj) {
-          cplx<double> g = project_one<MU>(pj[tj][(size_t)c6 * Ls], pj[tj][(size_t)lower_of<MU>(c6) * Ls], c6);
-          if (!in) g = {0, 0};
-#pragma unroll
-          for (int tk = 0; tk < T; ++tk) tile_step(g, hk[tk][c6], re[tj][tk], im[tj][tk]);
-        }
-      }
-    }
-  }
-}
-
-// -D_hop term of direction D added to `in` where it stays inside the block
-template <int D>
-__device__ __forceinline__ void inside_term(const StencilArgs& a, int vec, int p, long long h, int sr, const int c[4],
-                                            cplx<double> in[12]) {
-  if (leaves_block<D>(a, c)) return;
-  constexpr int MU = D / 2;
-  constexpr int SIGMA = (D % 2) ? +1 : -1;
-  const long long V4h = a.g.V4h;
-  const long long nh = __builtin_amdgcn_readfirstlane(a.nbr[((size_t)p * 8 + D) * V4h + h]);
-  cplx<double> psi[12], chi[6];
-  Store<DWF_F64>::load(half_of(a, vec, 1 - p), V4h, a.g.Ls, nh, sr, psi);
-  rotated_half<D>(a.links + ((size_t)(p * 8 + D) * 9) * V4h + h, V4h, psi, chi);
-  reconstruct<MU, SIGMA>(chi, in);
-}
-
-// The block itself: conj(phi_j(x, s)) gamma_5 [M5D phi_k - D_hop^{inside} phi_k / 2](x, Ls-1-s).
-template <int T>
-__device__ __forceinline__ void block_product(const StencilArgs& a, int b, const int (&vj)[T], const int (&vk)[T],
-                                              d4v (&re)[T][T], d4v (&im)[T][T]) {
-  const int q = (threadIdx.x & 63) >> 4;
-  const int Ls = a.g.Ls;
-  const long long V4h = a.g.V4h;
-  for (int i = threadIdx.x >> 6; i < a.nsb; i += WAVES) {
-    long long h;
-    int p, c[4];
-    block_site(a, b, __builtin_amdgcn_readfirstlane(i), h, p, c);
-    for (int s0 = 0; s0 < Ls; s0 += 4) {
-      const bool in = s0 + q < Ls;
-      const int s = in ? s0 + q : Ls - 1;
-      const int sr = Ls - 1 - s;
-      // M5D at the mirrored slice: (5 - M5) v_s - P_- v_{s+1} - P_+ v_{s-1}, the
-      // ends wrapping round with +mf instead of -1
-      const int su = sr + 1 < Ls ? sr + 1 : 0, sd = sr > 0 ? sr - 1 : Ls - 1;
-      const double cu = sr + 1 < Ls ? -1.0 : a.mf, cd = sr > 0 ? -1.0 : a.mf;
-      const double2* pj[T];  // phi_j is read as its components are needed: holding it would cost a wave per SIMD
-#pragma unroll
-      for (int t = 0; t < T; ++t)
-        pj[t] = reinterpret_cast<const double2*>(half_of(a, vj[t], p)) + h * 12 * Ls + s;
-#pragma unroll
-      for (int tk = 0; tk < T; ++tk) {
-        cplx<double> hop[12];
-#pragma unroll
-        for (int k = 0; k < 12; ++k) hop[k] = {0, 0};
-        inside_term<0>(a, vk[tk], p, h, sr, c, hop);
-        inside_term<1>(a, vk[tk], p, h, sr, c, hop);
-        inside_term<2>(a, vk[tk], p, h, sr, c, hop);
-        inside_term<3>(a, vk[tk], p, h, sr, c, hop);
-        inside_term<4>(a, vk[tk], p, h, sr, c, hop);
-        inside_term<5>(a, vk[tk], p, h, sr, c, hop);
-        inside_term<6>(a, vk[tk], p, h, sr, c, hop);
-        inside_term<7>(a, vk[tk], p, h, sr, c, hop);
-        __builtin_amdgcn_sched_barrier(0);  // the loads below, moved up, would not fit the registers
-        const double2* own = reinterpret_cast<const double2*>(half_of(a, vk[tk], p)) + h * 12 * Ls;
-#pragma unroll
-        for (int k = 0; k < 12; ++k) {
-          const double2 v0 = own[(size_t)k * Ls + sr];
-          const double2 v1 = own[(size_t)k * Ls + (k < 6 ? sd : su)];  // P_+ (upper spins) from below, P_- from above
-          const double c1 = k < 6 ? cd : cu;
-          cplx<double> m = {a.d * v0.x, a.d * v0.y};
-          m.re += c1 * v1.x;
-          m.im += c1 * v1.y;
-          m.re -= 0.5 * hop[k].re;
-          m.im -= 0.5 * hop[k].im;
-          const double sg = k < 6 ? 1.0 : -1.0;
-          m = {sg * m.re, sg * m.im};
-          if (!in) m = {0, 0};
-#pragma unroll
-          for (int tj = 0; tj < T; ++tj) {
-            const double2 f = pj[tj][(size_t)k * Ls];
-            tile_step(in ? cplx<double>{f.x, f.y} : cplx<double>{0, 0}, m, re[tj][tk], im[tj][tk]);
-          }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-  }
 }
 
 __device__ __forceinline__ void put(double2* p, double re, double im) { *p = make_double2(re, im); }
 __device__ __forceinline__ void put(float2* p, double re, double im) { *p = make_float2((float)re, (float)im); }
 
-// The workgroups of a block's five products follow each other on one XCD, so the
-// block's vectors are fetched into its L2 once; neighbouring blocks share an XCD.
-// The waves' sums are added in wave order through LDS.
-template <int T, class E>
-__global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(T == 3 ? 1 : 2)))
-stencil_kernel(StencilArgs a, E* __restrict__ A) {
-  __shared__ double red[WAVES][8][64];
-  const int slot = blockIdx.x >> 3;
-  const int point = slot % 5;  // 0..3 the forward faces, 4 the block itself
-  const int b = (blockIdx.x & 7) * a.nb8 + slot / 5;
+// Vectors come in groups of JT row tiles and KW column tiles, taken one after another;
+// the block's own n x n matrix waits in LDS (X) for its conjugate transpose.
+// Neighbouring blocks share an XCD.  NBUF = 2 buffers of staged vectors let a wave run
+// a step ahead of the others; where they do not fit (JT = 3) one is used.
+template <int JT, int KW, int NBUF, class E>
+__global__ void __launch_bounds__(256 * KW) __attribute__((amdgpu_waves_per_eu(2)))
+stencil_kernel(StencilArgs a, const double2* __restrict__ links, const int* __restrict__ bsite,
+               const int* __restrict__ nbr, E* __restrict__ A) {
+  extern __shared__ double2 smem[];
+  constexpr int NJ = 16 * JT, STRIDE = NJ + 1;  // padded: the staging writes go down columns
+  constexpr int BUF = 12 * SL * STRIDE;
+  constexpr int PER = NJ * 12 * SL / (256 * KW);  // staged values per thread
+  const int n = a.n, Ls = a.g.Ls;
+  const long long V4h = a.g.V4h;
+  double2* X = smem;  // [k][j]
+  double2* st = smem + n * n;
+  const int b = (blockIdx.x & 7) * a.nb8 + (blockIdx.x >> 3);
   if (b >= a.nb) return;  // whole workgroup leaves together
-  const int gj = blockIdx.y % a.groups, gk = blockIdx.y / a.groups;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int vj[T], vk[T];  // vectors of this lane; lanes past the last vector repeat it and store nothing
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int mu = wave & 3, kw = wave >> 2;
+  const int col = lane & 15, q = lane >> 4;
+  const int tiles = (n + 15) / 16;
+  const int chunks = (Ls + SL - 1) / SL;
+  const int nsteps = a.nsb * chunks;
+  const Direction dir(mu);
+  // local coordinate along mu of site i of the block: i / along % thick; a hop from the last
+  // one leaves the block unless the block wraps round the lattice
+  const int thick = a.blk[mu];
+  const int along = (mu > 0 ? a.blk[0] : 1) * (mu > 1 ? a.blk[1] : 1) * (mu > 2 ? a.blk[2] : 1);
+  const bool wraps = thick == (mu == 0 ? a.g.X : mu == 1 ? a.g.Y : mu == 2 ? a.g.Z : a.g.T);
+  // A step: a site and its first slice.
+  struct Step {
+    int i, p, s0;
+    long long h, nh;  // the site and its forward neighbour
+    int face;
+  };
+  auto at_site = [&](int i) {
+    Step w;
+    w.i = i;
+    w.s0 = 0;
+    const long long e = __builtin_amdgcn_readfirstlane(bsite[(size_t)b * a.nsb + i]);
+    w.p = e >= V4h ? 1 : 0;
+    w.h = e - w.p * V4h;
+    w.nh = __builtin_amdgcn_readfirstlane(nbr[((size_t)w.p * 8 + 2 * mu) * V4h + w.h]);
+    w.face = !wraps && i / along % thick == thick - 1 ? 1 : 0;
+    return w;
+  };
+  auto step_after = [&](Step w) {
+    w.s0 += SL;
+    return w.s0 < Ls ? w : at_site(w.i + 1);
+  };
+  const size_t nn = (size_t)n * n;
+  E* Ab = A + (size_t)b * 9 * nn;
+
+  for (int j0 = 0; j0 < tiles * 16; j0 += NJ)
+    for (int k0 = 0; k0 < tiles * 16; k0 += 16 * KW) {
+      const bool active = k0 + 16 * kw < n;  // uniform over the wave
+      const int vk = min(k0 + 16 * kw + col, n - 1);  // lanes past the last vector repeat it and store nothing
+      d4v fre[JT], fim[JT], ore[JT], oim[JT];
 #pragma unroll
-  for (int t = 0; t < T; ++t) {
-    vj[t] = min((gj * T + t) * 16 + (lane & 15), a.n - 1);
-    vk[t] = min((gk * T + t) * 16 + (lane & 15), a.n - 1);
-  }
-  d4v re[T][T], im[T][T];
+      for (int t = 0; t < JT; ++t) fre[t] = fim[t] = ore[t] = oim[t] = d4v{0, 0, 0, 0};
+      // This thread's share of a step's own vectors: one slice (consecutive threads,
+      // consecutive slices), vectors row % 16 + 16 t, every (2 KW)-th component
+      double2 pre[PER];
 #pragma unroll
-  for (int tj = 0; tj < T; ++tj)
+      for (int u = 0; u < PER; ++u) pre[u] = make_double2(0, 0);
+      const int s8 = threadIdx.x & (SL - 1), row = threadIdx.x / SL;
+      const int fv = row & 15, fc = row >> 4;
+      auto fetch = [&](const Step& w) {
+        if (w.s0 + s8 >= Ls) return;  // an idle slice keeps the values of an earlier one, which meet zeros
 #pragma unroll
-    for (int tk = 0; tk < T; ++tk) re[tj][tk] = im[tj][tk] = d4v{0, 0, 0, 0};
-  switch (point) {
-    case 0: face_product<0, T>(a, b, vj, vk, re, im); break;
-    case 1: face_product<1, T>(a, b, vj, vk, re, im); break;
-    case 2: face_product<2, T>(a, b, vj, vk, re, im); break;
-    case 3: face_product<3, T>(a, b, vj, vk, re, im); break;
-    default: block_product<T>(a, b, vj, vk, re, im); break;
-  }
-  const size_t nn = (size_t)a.n * a.n;
-  const double w = point < 4 ? -0.5 : 1.0;
-  E* own = A + ((size_t)b * 9 + (point < 4 ? 2 * point : 8)) * nn;
-  E* back = point < 4 ? A + ((size_t)a.bnbr[(size_t)b * 8 + 2 * point] * 9 + 2 * point + 1) * nn : nullptr;
+        for (int t = 0; t < JT; ++t) {
+          const char* f = a.basis + ((size_t)w.p * n + min(j0 + 16 * t + fv, n - 1)) * a.fb;
+          const double2* o = reinterpret_cast<const double2*>(f) + (w.h * 12 + fc) * Ls + w.s0 + s8;
 #pragma unroll
-  for (int tj = 0; tj < T; ++tj)
+          for (int u = 0; u < PER / JT; ++u) pre[t * (PER / JT) + u] = o[2 * KW * u * Ls];
+        }
+      };
+      auto mirrored = [&](int s0, int hf, bool& in) {
+        const int s = s0 + 4 * hf + q;
+        in = s < Ls;
+        return in ? Ls - 1 - s : 0;
+      };
+      // the two components per colour of spin sp of the forward neighbour's phi_k, for this lane's two slices
+      double2 ul[2][2][3];
+      auto load_spin = [&](const Step& w, int sp) {
+        const double2* f =
+            reinterpret_cast<const double2*>(a.basis + ((size_t)(1 - w.p) * n + vk) * a.fb) + w.nh * 12 * Ls;
+        const int lo = dir.lo[sp];
+        bool unused;
+        const int m0 = mirrored(w.s0, 0, unused), m1 = mirrored(w.s0, 1, unused);
 #pragma unroll
-    for (int tk = 0; tk < T; ++tk) {
-      __syncthreads();
+        for (int c = 0; c < 3; ++c) {  // both slices of a line together
+          ul[0][0][c] = f[(3 * sp + c) * Ls + m0];
+          ul[1][0][c] = f[(3 * sp + c) * Ls + m1];
+          ul[0][1][c] = f[(lo + c) * Ls + m0];
+          ul[1][1][c] = f[(lo + c) * Ls + m1];
+        }
+      };
+      Step cur = at_site(0), next = nsteps > 1 ? step_after(cur) : cur;
+      fetch(cur);
+      if (active) load_spin(cur, 0);
+      for (int step = 0; step < nsteps; ++step) {
+        const bool face = cur.face != 0;
+        int sr[2];
+        bool in[2];
+        sr[0] = mirrored(cur.s0, 0, in[0]);
+        sr[1] = mirrored(cur.s0, 1, in[1]);
+        double2* buf = st + (NBUF == 2 ? (step & 1) * BUF : 0);
+        {
+          double2* o = buf + (fc * SL + s8) * STRIDE + fv;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        red[wave][r][lane] = re[tj][tk][r];
-        red[wave][4 + r][lane] = im[tj][tk][r];
+          for (int t = 0; t < JT; ++t)
+#pragma unroll
+            for (int u = 0; u < PER / JT; ++u) o[2 * KW * u * SL * STRIDE + 16 * t] = pre[t * (PER / JT) + u];
+        }
+        __syncthreads();
+        fetch(next);
+        if (active) {
+          const double2* own = buf + q * STRIDE + col;
+          const double2* lk = links + ((size_t)(cur.p * 8 + 2 * mu) * 9) * V4h + cur.h;
+          // a fetch always has a spin's products to hide behind
+          cplx<double> chi[2][3];
+          rotate_spin(dir, 0, lk, V4h, ul, in, chi);
+          load_spin(cur, 1);
+          if (face)
+            hop_steps<JT>(dir, 0, own, STRIDE, chi, fre, fim);
+          else
+            hop_steps<JT>(dir, 0, own, STRIDE, chi, ore, oim);
+          rotate_spin(dir, 1, lk, V4h, ul, in, chi);
+          load_spin(next, 0);
+          if (face)
+            hop_steps<JT>(dir, 1, own, STRIDE, chi, fre, fim);
+          else
+            hop_steps<JT>(dir, 1, own, STRIDE, chi, ore, oim);
+          // components 3 mu .. 3 mu + 2 of the site-local part -gamma_5 M5D phi_k at the mirrored
+          // slice: (5 - M5) v_s - P_- v_{s+1} - P_+ v_{s-1}, the ends wrapping round with +mf
+          // instead of -1; P_+ (upper spins) from below, P_- from above.  The block's tiles are
+          // scaled by -1/2 and added to their conjugate transpose at the end: hence the sign.
+          const double2* phik =
+              reinterpret_cast<const double2*>(a.basis + ((size_t)cur.p * n + vk) * a.fb) + (cur.h * 12 + 3 * mu) * Ls;
+          const bool upper = mu < 2;
+          int s1[2];
+          double c0[2], c1[2];
+#pragma unroll
+          for (int hf = 0; hf < 2; ++hf) {
+            s1[hf] = upper ? (sr[hf] > 0 ? sr[hf] - 1 : Ls - 1) : (sr[hf] + 1 < Ls ? sr[hf] + 1 : 0);
+            const bool wrap = upper ? sr[hf] == 0 : sr[hf] + 1 == Ls;
+            const double sg = in[hf] ? (upper ? -1.0 : 1.0) : 0.0;
+            c0[hf] = sg * a.d;
+            c1[hf] = wrap ? sg * a.mf : -sg;
+          }
+#pragma unroll
+          for (int k = 0; k < 3; ++k) {
+            double2 v0[2], v1[2];  // one line, but for the slice beyond its end
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf) {
+              v0[hf] = phik[k * Ls + sr[hf]];
+              v1[hf] = phik[k * Ls + s1[hf]];
+            }
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf) {
+              const cplx<double> m = {c0[hf] * v0[hf].x + c1[hf] * v1[hf].x, c0[hf] * v0[hf].y + c1[hf] * v1[hf].y};
+#pragma unroll
+              for (int t = 0; t < JT; ++t) {
+                const double2 f = own[((3 * mu + k) * SL + 4 * hf) * STRIDE + 16 * t];
+                tile_step(cplx<double>{f.x, f.y}, m, ore[t], oim[t]);
+              }
+            }
+          }
+        }
+        cur = next;
+        if (step + 2 < nsteps) next = step_after(next);
+        if (NBUF == 1) __syncthreads();
       }
-      __syncthreads();
-      // thread (r, lane) of the tile: row j = lane / 16 + 4 r, column k = lane % 16
-      const int r = wave;
-      double sr = 0, si = 0;
+      // register r of a tile: row j = lane / 16 + 4 r, column k = lane % 16
+      const int k = k0 + 16 * kw + col;
+      E* own = Ab + (size_t)(2 * mu) * nn;
+      E* back = A + ((size_t)a.bnbr[(size_t)b * 8 + 2 * mu] * 9 + 2 * mu + 1) * nn;
 #pragma unroll
-      for (int v = 0; v < WAVES; ++v) {
-        sr += red[v][r][lane];
-        si += red[v][4 + r][lane];
-      }
-      const int j = (gj * T + tj) * 16 + (lane >> 4) + 4 * r;
-      const int k = (gk * T + tk) * 16 + (lane & 15);
-      if (j < a.n && k < a.n) {
-        put(own + (size_t)k * a.n + j, w * sr, w * si);
-        if (back) put(back + (size_t)j * a.n + k, w * sr, -(w * si));
+      for (int t = 0; t < JT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int j = j0 + 16 * t + q + 4 * r;
+          if (j < n && k < n) {
+            put(own + (size_t)k * n + j, -0.5 * fre[t][r], -0.5 * fim[t][r]);
+            put(back + (size_t)j * n + k, -0.5 * fre[t][r], 0.5 * fim[t][r]);
+          }
+        }
+      for (int m = 0; m < 4; ++m) {  // the directions' parts of the block itself, added in order
+        if (mu == m) {
+#pragma unroll
+          for (int t = 0; t < JT; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const int j = j0 + 16 * t + q + 4 * r;
+              if (j < n && k < n) {
+                double2 x = m ? X[(size_t)k * n + j] : make_double2(0, 0);
+                X[(size_t)k * n + j] = make_double2(x.x - 0.5 * ore[t][r], x.y - 0.5 * oim[t][r]);
+              }
+            }
+        }
+        __syncthreads();
       }
     }
+  for (int idx = threadIdx.x; idx < (int)nn; idx += 256 * KW) {
+    const int k = idx / n, j = idx - k * n;
+    const double2 x = X[idx], y = X[j * n + k];
+    put(Ab + 8 * nn + idx, x.x + y.x, x.y - y.y);
+  }
 }
 
-template <class E>
-hipError_t launch_t(dwf_context* c, StencilArgs& a, E* A) {
-  // one group of T x T tiles holds up to 48 vectors in registers; 49 to 64 take four groups of 2 x 2
-  const int tiles = (a.n + 15) / 16;
-  const int T = tiles == 4 ? 2 : tiles;
-  a.groups = (tiles + T - 1) / T;
-  const dim3 grid((unsigned)a.nb8 * 8 * 5, (unsigned)(a.groups * a.groups)), block(64 * WAVES);
-  switch (T) {
-    case 1: hipLaunchKernelGGL((stencil_kernel<1, E>), grid, block, 0, c->stream, a, A); break;
-    case 2: hipLaunchKernelGGL((stencil_kernel<2, E>), grid, block, 0, c->stream, a, A); break;
-    default: hipLaunchKernelGGL((stencil_kernel<3, E>), grid, block, 0, c->stream, a, A); break;
-  }
+template <int JT, int KW, int NBUF, class E>
+hipError_t launch_s(dwf_context* c, const StencilArgs& a, E* A) {
+  const size_t lds = ((size_t)a.n * a.n + (size_t)NBUF * 12 * SL * (16 * JT + 1)) * sizeof(double2);
+  hipLaunchKernelGGL((stencil_kernel<JT, KW, NBUF, E>), dim3((unsigned)a.nb8 * 8), dim3(256 * KW), lds, c->stream, a,
+                     reinterpret_cast<const double2*>(c->links64), c->bsite, c->nbr, A);
   return hipGetLastError();
+}
+
+// Row tiles per group: as many as the registers of two waves per SIMD hold (three); 49 to
+// 64 vectors take two groups of two.  LDS: 56, 117, 112 and 116 KB of a CU's 160 at
+// n = 16, 32, 48 and 64.
+template <class E>
+hipError_t launch_t(dwf_context* c, const StencilArgs& a, E* A) {
+  switch ((a.n + 15) / 16) {
+    case 1: return launch_s<1, 1, 2>(c, a, A);
+    case 2: return launch_s<2, 2, 2>(c, a, A);
+    case 3: return launch_s<3, 2, 1>(c, a, A);
+    default: return launch_s<2, 2, 1>(c, a, A);
+  }
 }
 
 }  // namespace
@@ -332,9 +367,6 @@ hipError_t launch_stencil(dwf_context* c, const char* basis, int nvec, int prec,
   a.n = nvec;
   a.d = 5.0 - c->M5;
   a.mf = c->mf;
-  a.links = reinterpret_cast<const double2*>(c->links64);
-  a.nbr = c->nbr;
-  a.bsite = c->bsite;
   a.bnbr = c->bnbr;
   a.basis = basis;
   a.fb = field_bytes_rhs(c, DWF_F64);
