@@ -1135,9 +1135,9 @@ static int gs_cholqr2(dwf_handle h, char* Q, int n, std::vector<double>& Rout) {
   const size_t cap = fbytes(h, P) * (size_t)h->partial_count;
   const size_t per = nn * 2 * sizeof(double);
   if (cap < 2 * per) return GS_USE_CGS2;
-  const long long m = h->g.V4h * h->g.Ls * 12;
+  // ranges of the lattice, one per workgroup: two for every CU, four sites (one a wave) at least
   long long nwg = (long long)(cap / per) - 1;
-  nwg = std::min<long long>({nwg, 2048, (m + 255) / 256});
+  nwg = std::min<long long>({nwg, 512, (h->g.V4h + 3) / 4});
   if (nwg < 1) return GS_USE_CGS2;
   double* partial = reinterpret_cast<double*>(h->t_buf);
   double* Gd = partial + 2 * nn * (size_t)nwg;
@@ -1333,7 +1333,7 @@ int dwf_restrict(dwf_handle h, const void* basis, int nvec, const void* v, int n
   if (int r = check_blocks(h, nvec, "dwf_restrict")) return r;
   if (!basis || !v || !coarse || nrhs < 1) return fail(DWF_EINVAL, "dwf_restrict: NULL pointer or nrhs < 1");
   HIP_TRY(launch_block_dot(h, h->prec, reinterpret_cast<const char*>(basis), nvec, reinterpret_cast<const char*>(v),
-                           nrhs, reinterpret_cast<double*>(coarse), false));
+                           nrhs, reinterpret_cast<double*>(coarse)));
   return DWF_OK;
 }
 

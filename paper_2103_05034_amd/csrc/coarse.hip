@@ -13,10 +13,11 @@
 //   v_{Ls-1-s}: the five-dimensional chirality used when the domain-wall
 //   operator is coarsened (Deflation basis setup section).
 // * block_dot: c[r][b][k] = <phi_k^b, v_r>, the restrictor applied to nrhs
-//   fields; with v = the basis itself it is the Gram matrix of every block.
+//   fields.
 // * block_combine: out_r = sum_k c[r][b][k] phi_k^b (prolongator), or the
 //   in-place map phi_k <- sum_{j<=k} W[b][j][k] phi_j^b used to
-//   orthonormalise (W = R^{-1} of the block's Cholesky factor).
+//   orthonormalise FP16 + scale fields (W = R^{-1} of the block's Cholesky
+//   factor); the other precisions and the Gram matrices are in gram.hip.
 // * block_cholesky: per block G = R^dag R, then W = R^{-1}.
 //
 // One workgroup owns one block; its lane p = j * Ls + s holds one 5D site of
@@ -100,7 +101,6 @@ struct BlockArgs {
   char* out;      // block_combine: output fields (or the basis itself, in place)
   int nrhs;
   double* coef;        // block_dot output / block_combine input, complex [nrhs][nb][nvec]
-  int per_block;       // block_dot: lay coef out as [nb][nrhs][nvec] (each block's Gram matrix contiguous)
   const double* wmat;  // block_combine in-place mode: complex [nb][nvec][nvec], W[j][k] at (j * nvec + k)
 };
 
@@ -148,9 +148,7 @@ __global__ void __launch_bounds__(512) block_dot_kernel(BlockArgs a) {
       for (int c = 0; c < 12; ++c) v[q][r][c] = {0, 0};
       if (use) Store<P>::load(a.v + par[q] * a.v_ps + (size_t)(r0 + r) * a.stride, a.g.V4h, a.g.Ls, h[q], s[q], v[q][r]);
     }
-  // a Gram matrix (per_block) is Hermitian and its Cholesky factorisation reads
-  // only the entries with basis index <= rhs index: stop at the tile's last rhs
-  const int kend = a.per_block ? min(a.nvec, r0 + RT) : a.nvec;
+  const int kend = a.nvec;
   for (int k0 = 0; k0 < kend; k0 += KG) {
     double acc[2 * RT * KG];
 #pragma unroll
@@ -185,101 +183,12 @@ __global__ void __launch_bounds__(512) block_dot_kernel(BlockArgs a) {
 #pragma unroll
         for (int kk = 0; kk < KG; ++kk)
           if (r0 + r < a.nrhs && k0 + kk < kend) {
-            const size_t row = a.per_block ? (size_t)b * a.nrhs + r0 + r : (size_t)(r0 + r) * a.nb + b;
+            const size_t row = (size_t)(r0 + r) * a.nb + b;
             double* o = a.coef + 2 * (row * a.nvec + k0 + kk);
             o[0] = acc[2 * (r * KG + kk)];
             o[1] = acc[2 * (r * KG + kk) + 1];
           }
     }
-  }
-}
-
-// Gram matrix of every block, G[b][k][j] = <phi_j^b, phi_k^b> for j <= k, with
-// each basis vector read once: the block's rows (5D site x colour-spin
-// component) pass through LDS in chunks of `chunk` 5D sites, all nvec
-// vectors at once, and every thread accumulates 2 x 2 tiles of (j, k) pairs
-// in FP64 from the staged rows.
-constexpr int GRAM_TPT = 4;  // tiles per thread: (n/2)(n/2+1)/2 <= 528 for n <= 64
-
-template <int P>
-__global__ void __launch_bounds__(256) block_gram_kernel(BlockArgs a, int chunk) {
-  using R = typename Store<P>::real;
-  extern __shared__ char smem[];
-  cplx<R>* sm = reinterpret_cast<cplx<R>*>(smem);  // [chunk * 12][n]
-  const int b = blockIdx.x;
-  const int n = a.nvec;
-  const int Ls = a.g.Ls;
-  const int np = a.nsb * Ls;
-  const int half = (n + 1) / 2;
-  const int ntiles = half * (half + 1) / 2;
-  double acc[GRAM_TPT][8];
-  int ta[GRAM_TPT], tb[GRAM_TPT];
-#pragma unroll
-  for (int q = 0; q < GRAM_TPT; ++q) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) acc[q][i] = 0;
-    // tile index -> (ta <= tb): row-major over the upper triangle
-    int t = threadIdx.x + q * blockDim.x, row = 0;
-    while (t >= half - row && row < half) {
-      t -= half - row;
-      ++row;
-    }
-    ta[q] = row;
-    tb[q] = row + t;
-  }
-  for (int p0 = 0; p0 < np; p0 += chunk) {
-    const int cs = min(chunk, np - p0);
-    __syncthreads();  // previous chunk consumed
-    for (int item = threadIdx.x; item < cs * n; item += blockDim.x) {
-      const int j = item / cs, pl = item - j * cs;  // consecutive threads: consecutive 5D sites
-      const int p = p0 + pl;
-      const int site = p / Ls, s = p - site * Ls;
-      long long h = a.bsite[(size_t)b * a.nsb + site];
-      const int par = split_site(a.g.V4h, h);
-      cplx<R> f[12];
-      Store<P>::load(a.basis + par * a.basis_ps + (size_t)j * a.stride, a.g.V4h, Ls, h, s, f);
-#pragma unroll
-      for (int c = 0; c < 12; ++c) sm[(size_t)(pl * 12 + c) * n + j] = f[c];
-    }
-    __syncthreads();
-    const int rows = cs * 12;
-#pragma unroll
-    for (int q = 0; q < GRAM_TPT; ++q) {
-      if (threadIdx.x + q * blockDim.x >= ntiles) continue;
-      const int j0 = 2 * ta[q], k0 = 2 * tb[q];
-      const bool j1 = j0 + 1 < n, k1 = k0 + 1 < n;
-      for (int r = 0; r < rows; ++r) {
-        const cplx<R>* row = sm + (size_t)r * n;
-        const cplx<R> x0 = row[j0], y0 = row[k0];
-        const cplx<R> x1 = j1 ? row[j0 + 1] : cplx<R>{0, 0};
-        const cplx<R> y1 = k1 ? row[k0 + 1] : cplx<R>{0, 0};
-        // conj(x) y
-        acc[q][0] = fma((double)x0.re, (double)y0.re, fma((double)x0.im, (double)y0.im, acc[q][0]));
-        acc[q][1] = fma((double)x0.re, (double)y0.im, fma(-(double)x0.im, (double)y0.re, acc[q][1]));
-        acc[q][2] = fma((double)x0.re, (double)y1.re, fma((double)x0.im, (double)y1.im, acc[q][2]));
-        acc[q][3] = fma((double)x0.re, (double)y1.im, fma(-(double)x0.im, (double)y1.re, acc[q][3]));
-        acc[q][4] = fma((double)x1.re, (double)y0.re, fma((double)x1.im, (double)y0.im, acc[q][4]));
-        acc[q][5] = fma((double)x1.re, (double)y0.im, fma(-(double)x1.im, (double)y0.re, acc[q][5]));
-        acc[q][6] = fma((double)x1.re, (double)y1.re, fma((double)x1.im, (double)y1.im, acc[q][6]));
-        acc[q][7] = fma((double)x1.re, (double)y1.im, fma(-(double)x1.im, (double)y1.re, acc[q][7]));
-      }
-    }
-  }
-  // G[b][k][j] = <phi_j, phi_k>, j <= k
-  double* G = a.coef + 2 * (size_t)b * n * n;
-#pragma unroll
-  for (int q = 0; q < GRAM_TPT; ++q) {
-    if (threadIdx.x + q * blockDim.x >= ntiles) continue;
-    const int j0 = 2 * ta[q], k0 = 2 * tb[q];
-#pragma unroll
-    for (int dj = 0; dj < 2; ++dj)
-#pragma unroll
-      for (int dk = 0; dk < 2; ++dk) {
-        const int j = j0 + dj, k = k0 + dk;
-        if (j >= n || k >= n || j > k) continue;
-        G[2 * (k * n + j)] = acc[q][2 * (2 * dj + dk)];
-        G[2 * (k * n + j) + 1] = acc[q][2 * (2 * dj + dk) + 1];
-      }
   }
 }
 
@@ -363,70 +272,62 @@ __global__ void __launch_bounds__(512) block_combine_kernel(BlockArgs a) {
 }
 
 // Per block: Cholesky G = R^dag R of the Hermitian Gram matrix
-// G[k][j] = <phi_j, phi_k> (as block_dot lays it out, row = rhs = k; only
-// j <= k is read), then W = R^{-1}, upper triangular, stored W[j][k] at
-// (j * n + k).  One wave per block, lane k owning column k: row j of R is
-// R[j][k] = (G_jk - sum_{i<j} conj(R[i][j]) R[i][k]) / R[j][j], computed by
-// all lanes k >= j at once from column j (finished by lane j in the step
-// before); column k of R^{-1} then needs only R and the lane's own column.
-// A non-positive or non-finite pivot raises *flag.
-__global__ void __launch_bounds__(64) block_cholesky_kernel(const double* __restrict__ gram, double* __restrict__ w,
+// G[k][j] = <phi_j, phi_k> (only j <= k is read), then W = R^{-1}, upper
+// triangular, stored W[j][k] at (j * n + k).  One wave per block, lane k owning
+// column k: row j of R is R[j][k] = (G_jk - sum_{i<j} conj(R[i][j]) R[i][k]) / R[j][j],
+// computed by all lanes k >= j at once, the diagonal among them; column k of
+// R^{-1} then needs only R and the lane's own column.  R and W stay in LDS: a
+// column read back from memory at every step made this a chain of memory
+// round trips (0.44 ms for 2048 blocks of 40 vectors).  A non-positive or
+// non-finite pivot raises *flag.
+__global__ void __launch_bounds__(64) block_cholesky_kernel(const double2* __restrict__ gram, double2* __restrict__ w,
                                                             int nb, int n, int* flag) {
-  extern __shared__ double rs[];  // R, complex [n][n]
+  extern __shared__ double2 rs[];  // R [n][n], then W [n][n]
+  double2* ws = rs + n * n;
   const int b = blockIdx.x;
   const int k = threadIdx.x;
-  const double* G = gram + 2 * (size_t)b * n * n;
-  double* W = w + 2 * (size_t)b * n * n;
-  for (int i = k; i < n * n; i += 64) {
-    rs[2 * i] = 0.0;
-    rs[2 * i + 1] = 0.0;
-  }
+  const double2* G = gram + (size_t)b * n * n;
+  for (int i = k; i < n * n; i += 64) ws[i] = G[i];  // G waits where W will be, entry (k, j) at k * n + j
   __syncthreads();
   for (int j = 0; j < n; ++j) {
-    if (k == j) {
-      double d = G[2 * (j * n + j)];
-      for (int i = 0; i < j; ++i) d -= rs[2 * (i * n + j)] * rs[2 * (i * n + j)] + rs[2 * (i * n + j) + 1] * rs[2 * (i * n + j) + 1];
-      if (!(d > 0.0) || !isfinite(d)) {
-        *flag = 1;
-        d = 1.0;
-      }
-      rs[2 * (j * n + j)] = sqrt(d);
-    }
-    __syncthreads();
-    if (k > j && k < n) {
-      double re = G[2 * (k * n + j)], im = G[2 * (k * n + j) + 1];  // G_jk = <phi_j, phi_k>
-      for (int i = 0; i < j; ++i) {
-        const double ar = rs[2 * (i * n + j)], ai = -rs[2 * (i * n + j) + 1];  // conj(R[i][j])
-        const double br = rs[2 * (i * n + k)], bi = rs[2 * (i * n + k) + 1];
-        re -= ar * br - ai * bi;
-        im -= ar * bi + ai * br;
-      }
-      const double inv = 1.0 / rs[2 * (j * n + j)];
-      rs[2 * (j * n + k)] = re * inv;
-      rs[2 * (j * n + k) + 1] = im * inv;
-    }
-    __syncthreads();
-  }
-  if (k >= n) return;
-  // column k of R^{-1}: W[k][k] = 1 / R[k][k]; W[j][k] = -(sum_{i=j+1..k} R[j][i] W[i][k]) / R[j][j]
-  for (int j = k + 1; j < n; ++j) {
-    W[2 * (j * n + k)] = 0.0;
-    W[2 * (j * n + k) + 1] = 0.0;
-  }
-  W[2 * (k * n + k)] = 1.0 / rs[2 * (k * n + k)];
-  W[2 * (k * n + k) + 1] = 0.0;
-  for (int j = k - 1; j >= 0; --j) {
     double re = 0, im = 0;
-    for (int i = j + 1; i <= k; ++i) {
-      const double ar = rs[2 * (j * n + i)], ai = rs[2 * (j * n + i) + 1];
-      const double br = W[2 * (i * n + k)], bi = W[2 * (i * n + k) + 1];
-      re += ar * br - ai * bi;
-      im += ar * bi + ai * br;
+    if (k >= j && k < n) {
+      const double2 g = ws[k * n + j];  // G_jk = <phi_j, phi_k>
+      re = g.x;
+      im = g.y;
+      for (int i = 0; i < j; ++i) {
+        const double2 c = rs[i * n + j], r = rs[i * n + k];  // conj(R[i][j]) R[i][k]
+        re -= c.x * r.x + c.y * r.y;
+        im -= c.x * r.y - c.y * r.x;
+      }
     }
-    const double inv = -1.0 / rs[2 * (j * n + j)];
-    W[2 * (j * n + k)] = re * inv;
-    W[2 * (j * n + k) + 1] = im * inv;
+    double d = __shfl(re, j);
+    if (!(d > 0.0) || !isfinite(d)) {
+      if (k == j) *flag = 1;
+      d = 1.0;
+    }
+    const double root = sqrt(d), inv = 1.0 / root;
+    if (k >= j && k < n) rs[j * n + k] = k == j ? make_double2(root, 0.0) : make_double2(re * inv, im * inv);
+    __syncthreads();
   }
+  // column k of R^{-1}: W[k][k] = 1 / R[k][k]; W[j][k] = -(sum_{i=j+1..k} R[j][i] W[i][k]) / R[j][j]
+  if (k < n) {
+    for (int j = k + 1; j < n; ++j) ws[j * n + k] = make_double2(0.0, 0.0);
+    ws[k * n + k] = make_double2(1.0 / rs[k * n + k].x, 0.0);
+    for (int j = k - 1; j >= 0; --j) {
+      double re = 0, im = 0;
+      for (int i = j + 1; i <= k; ++i) {
+        const double2 r = rs[j * n + i], v = ws[i * n + k];
+        re += r.x * v.x - r.y * v.y;
+        im += r.x * v.y + r.y * v.x;
+      }
+      const double inv = -1.0 / rs[j * n + j].x;
+      ws[j * n + k] = make_double2(re * inv, im * inv);
+    }
+  }
+  __syncthreads();
+  double2* W = w + (size_t)b * n * n;
+  for (int i = k; i < n * n; i += 64) W[i] = ws[i];
 }
 
 // ---------------------------------------------------------------------------
@@ -484,13 +385,12 @@ static void dot_p(const dwf_context* c, const BlockArgs& a) {
 }
 
 hipError_t launch_block_dot(dwf_context* c, int prec, const char* basis, int nvec, const char* v, int nrhs,
-                            double* coef, bool per_block) {
+                            double* coef) {
   BlockArgs a = block_args(c, prec, basis, nvec);
   a.v = v;
   a.nrhs = nrhs;
   a.v_ps = c->coarse_both ? (size_t)nrhs * a.stride : 0;
   a.coef = coef;
-  a.per_block = per_block ? 1 : 0;
   switch (prec) {
     case DWF_F64: dot_p<DWF_F64>(c, a); break;
     case DWF_F32: dot_p<DWF_F32>(c, a); break;
@@ -523,37 +423,18 @@ hipError_t launch_block_prolong(dwf_context* c, int prec, const char* basis, int
 }
 
 hipError_t launch_block_apply(dwf_context* c, int prec, char* basis, int nvec, const double* wmat) {
+  if (prec != DWF_F16S) return launch_block_apply_mfma(c, prec, basis, nvec, wmat);
   BlockArgs a = block_args(c, prec, basis, nvec);
   a.wmat = wmat;
   a.out = basis;
   a.out_ps = a.basis_ps;
-  switch (prec) {
-    case DWF_F64: combine_t<DWF_F64, 2, true>(c, a); break;
-    case DWF_F32: combine_t<DWF_F32, 2, true>(c, a); break;
-    default: combine_t<DWF_F16S, 2, true>(c, a); break;
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_block_gram(dwf_context* c, int prec, const char* basis, int nvec, double* gram) {
-  BlockArgs a = block_args(c, prec, basis, nvec);
-  a.coef = gram;
-  const size_t cb = prec == DWF_F64 ? 16 : 8;
-  const size_t budget = 48 * 1024;
-  int chunk = (int)(budget / (12 * (size_t)nvec * cb));  // 5D sites staged per pass
-  if (chunk < 1) chunk = 1;
-  const size_t lds = (size_t)chunk * 12 * nvec * cb;
-  switch (prec) {
-    case DWF_F64: hipLaunchKernelGGL(block_gram_kernel<DWF_F64>, dim3(a.nb), dim3(256), lds, c->stream, a, chunk); break;
-    case DWF_F32: hipLaunchKernelGGL(block_gram_kernel<DWF_F32>, dim3(a.nb), dim3(256), lds, c->stream, a, chunk); break;
-    default: hipLaunchKernelGGL(block_gram_kernel<DWF_F16S>, dim3(a.nb), dim3(256), lds, c->stream, a, chunk); break;
-  }
+  combine_t<DWF_F16S, 2, true>(c, a);
   return hipGetLastError();
 }
 
 hipError_t launch_block_cholesky(dwf_context* c, const double* gram, double* w, int nvec, int* flag) {
-  hipLaunchKernelGGL(block_cholesky_kernel, dim3(c->nb), dim3(64), (size_t)nvec * nvec * 2 * sizeof(double), c->stream,
-                     gram, w, c->nb, nvec, flag);
+  hipLaunchKernelGGL(block_cholesky_kernel, dim3(c->nb), dim3(64), (size_t)nvec * nvec * 2 * sizeof(double2), c->stream,
+                     reinterpret_cast<const double2*>(gram), reinterpret_cast<double2*>(w), c->nb, nvec, flag);
   return hipGetLastError();
 }
 

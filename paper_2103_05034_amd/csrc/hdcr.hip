@@ -492,7 +492,7 @@ int coarse_cgnr(dwf_hdcr_s* hd, const double2* d, double2* cvec, double tol, int
 // out = Q r = P A^{-1} P^dag r
 int coarse_correction(dwf_hdcr_s* hd, const char* r, char* out) {
   dwf_context* c = hd->h;
-  HIP_TRY(launch_block_dot(c, DWF_F64, hd->basis, hd->nvec, r, 1, reinterpret_cast<double*>(hd->cv[0]), false));
+  HIP_TRY(launch_block_dot(c, DWF_F64, hd->basis, hd->nvec, r, 1, reinterpret_cast<double*>(hd->cv[0])));
   if (int rc = coarse_cgnr(hd, hd->cv[0], hd->cv[1], hd->prm.coarse_tol, hd->prm.coarse_maxiter, nullptr)) return rc;
   HIP_TRY(launch_block_prolong(c, DWF_F64, hd->basis, hd->nvec, reinterpret_cast<const double*>(hd->cv[1]), 1, out));
   return DWF_OK;

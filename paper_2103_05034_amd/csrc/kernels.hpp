@@ -118,25 +118,27 @@ hipError_t gs_multidot(dwf_context* ctx, int prec, const char* Q, const char* v,
 hipError_t gs_multiaxpy(dwf_context* ctx, int prec, const char* Q, char* v, int j, const double* coef);
 // Cholesky-QR pieces for up to TS_NMAX fields at any storage precision (fields
 // consecutive at field_bytes_rhs apart).  ts_gram: G[k][j] =
-// <v_j, v_k> for j <= k (complex FP64, n x n) from nwg per-workgroup partial sums in
-// `partial` (nwg * n * n complex), added in workgroup order.  ts_combine: in place
+// <v_j, v_k> for j <= k (complex FP64, n x n) from at most nwg per-workgroup partial sums in
+// `partial` (nwg * n * n complex), added in a fixed order.  ts_combine: in place
 // v_k <- sum_{j <= k} W[j][k] v_j (W upper triangular, complex FP64, W[j][k] at j * n + k).
 constexpr int TS_NMAX = 64;
 hipError_t ts_gram(dwf_context* ctx, int prec, const char* V, int n, double* partial, int nwg, double* G);
 hipError_t ts_combine(dwf_context* ctx, int prec, char* V, int n, const double* W);
+hipError_t ts_combine_mfma(dwf_context* ctx, int prec, char* V, int n, const double* W);  // FP64, FP32
 hipError_t gs_scale(dwf_context* ctx, int prec, char* v, const double* inv_norm);
 
 // coarse.hip (block tables in ctx->bsite; coefficients complex FP64)
 hipError_t launch_chiral_split(dwf_context* c, int prec, const char* in, char* out, int nvec);
-// coef[r][b][k] = <phi_k^b, v_r> ([b][r][k] with per_block)
+// coef[r][b][k] = <phi_k^b, v_r>
 hipError_t launch_block_dot(dwf_context* c, int prec, const char* basis, int nvec, const char* v, int nrhs,
-                            double* coef, bool per_block);
+                            double* coef);
 // out_r = sum_k coef[r][b][k] phi_k^b
 hipError_t launch_block_prolong(dwf_context* c, int prec, const char* basis, int nvec, const double* coef, int nrhs,
                                 char* out);
 // phi_k <- sum_{j<=k} W[b][j][k] phi_j^b in place
 hipError_t launch_block_apply(dwf_context* c, int prec, char* basis, int nvec, const double* wmat);
-// per block: Gram matrix [b][k][j] = <phi_j, phi_k> (j <= k) with each vector read once
+hipError_t launch_block_apply_mfma(dwf_context* c, int prec, char* basis, int nvec, const double* wmat);  // FP64, FP32
+// per block: Gram matrix [b][k][j] = <phi_j, phi_k> (j <= k) (gram.hip)
 hipError_t launch_block_gram(dwf_context* c, int prec, const char* basis, int nvec, double* gram);
 // per block: Cholesky of the Gram matrix ([b][k][j] = <phi_j, phi_k>) and W = R^{-1}
 hipError_t launch_block_cholesky(dwf_context* c, const double* gram, double* w, int nvec, int* flag);

@@ -229,3 +229,59 @@ def test_blocks_of_1024_5d_sites(both, block):
     got = unpack(op, op.prolong(basis, 6, torch.from_numpy(cc).cuda(), 2), 2, parity)
     for r in range(2):
         assert relmax(got[r], C.prolong(list(Q), cc[r], dims, block)) < 1e-14
+
+
+@pytest.mark.parametrize("prec,unit", [(F64, 2.0**-53), (F32, 2.0**-24), (F16S, 2.0**-11)])
+@pytest.mark.parametrize(
+    "dims, Ls, block, nvec, both",
+    [
+        ((4, 4, 4, 4), 3, (2, 2, 2, 2), 1, False),  # one vector; a site of 36 values, no whole number of lines
+        ((4, 4, 4, 4), 5, (2, 2, 2, 4), 8, False),  # one full tile of eight vectors
+        ((4, 4, 4, 4), 4, (2, 2, 2, 2), 9, True),  # one vector into the second tile; both parities
+        ((4, 4, 4, 6), 7, (2, 2, 2, 2), 40, True),  # five full tiles
+        ((4, 4, 4, 4), 6, (4, 2, 4, 2), 49, False),  # seven tiles
+        ((4, 4, 4, 4), 8, (2, 2, 2, 2), 57, True),  # eight tiles: the products in two launches
+        ((4, 4, 4, 4), 16, (2, 2, 2, 2), 64, False),  # the most vectors
+    ],
+)
+def test_block_orthonormalize_tiles(prec, unit, dims, Ls, block, nvec, both):
+    parity = 2 if both else EVEN
+    op, _ = make_operator(dims, Ls, prec=prec, max_nrhs=2)
+    op.set_blocks(block, both=both)
+    raw = synth.gaussian_fermion_batch(dims, Ls, nvec, 46)
+    buf = pack(op, raw if both else L.on_parity(raw, EVEN), parity)
+    held = unpack(op, buf, nvec, parity)
+    op.block_orthonormalize(buf, nvec)
+    Q = unpack(op, buf, nvec, parity)
+    Qo, _ = C.block_orthonormalize(list(held), dims, block)
+    # Each of the two rounds rounds every value once to the storage (relative to the spinor's largest for
+    # FP16 + scale: sqrt(24) of its norm at most), the first error passing through the second round's R;
+    # the FP64 sums over a block's K values add K u.  All of it grows at most with the condition number
+    # squared: (1 + r) / (1 - r) with r = sqrt(n / K) for Gaussian vectors, 20 % above it over the blocks.
+    K = 12 * Ls * int(np.prod(block)) / (1 if both else 2)
+    r = np.sqrt(nvec / K)
+    cond = 1.2 * (1 + r) / (1 - r)
+    tol = 4 * unit * cond**2 * (np.sqrt(24) if prec == F16S else 1) + K * 2.0**-53 * cond**2
+    big = max(float(np.max(np.abs(q))) for q in Qo)
+    for k in range(nvec):
+        assert np.max(np.abs(Q[k] - Qo[k])) < tol * max(big, 1.0), k
+
+
+@pytest.mark.parametrize("prec,unit", [(F64, 2.0**-53), (F32, 2.0**-24)])
+@pytest.mark.parametrize("dims, Ls, nvec", [((4, 4, 4, 6), 3, 9), ((2, 4, 6, 4), 5, 24), ((4, 4, 6, 4), 7, 56)])
+def test_gram_schmidt_ragged_sites(prec, unit, dims, Ls, nvec):
+    """Whole-lattice Cholesky QR where a site's values end inside a line and the ranges of sites are unequal."""
+    from oracle import krylov
+
+    op, _ = make_operator(dims, Ls, prec=prec, max_nrhs=3)
+    buf = pack(op, even_fields(dims, Ls, nvec, seed=47), EVEN)
+    held = unpack(op, buf, nvec, EVEN)
+    R = op.gram_schmidt(buf, nvec)
+    Q = unpack(op, buf, nvec, EVEN)
+    Qo, Ro = krylov.gram_schmidt(list(held))
+    K = 6 * Ls * int(np.prod(dims))
+    r = np.sqrt(nvec / K)
+    tol = (4 * unit + K * 2.0**-53) * (1.2 * (1 + r) / (1 - r)) ** 2  # as above
+    for k in range(nvec):
+        assert np.max(np.abs(Q[k] - Qo[k])) < tol * max(1.0, float(np.max(np.abs(Qo[k]))))
+    assert np.max(np.abs(R - Ro)) < tol * np.max(np.abs(Ro))
