@@ -56,39 +56,6 @@ __global__ void __launch_bounds__(CB) g5_combine_kernel(long long nsite, int Ls,
   out[i] = o;
 }
 
-// y[b] = sum_r A[b][r] x[neighbour_r(b)]: one workgroup per block, lane j
-// computes row j; the nine input vectors pass through LDS.
-template <class T>
-__global__ void __launch_bounds__(64) coarse_matvec_kernel(const T* __restrict__ A, const int* __restrict__ bnbr,
-                                                           int n, const double2* __restrict__ x,
-                                                           double2* __restrict__ y) {
-  __shared__ double2 xs[9 * 64];
-  const int b = blockIdx.x;
-  for (int i = threadIdx.x; i < 9 * n; i += 64) {
-    const int r = i / n, k = i - r * n;
-    const int src = r < 8 ? bnbr[(size_t)b * 8 + r] : b;
-    xs[i] = x[(size_t)src * n + k];
-  }
-  __syncthreads();
-  const int j = threadIdx.x;
-  if (j >= n) return;
-  double re = 0, im = 0;
-  const T* Ab = A + (size_t)b * 9 * n * n;
-  for (int r = 0; r < 9; ++r)
-    for (int k = 0; k < n; ++k) {
-      // each entry is read once per matvec: non-temporal loads (-10 % time in complex128)
-      typedef typename std::conditional<sizeof(T) == 16, double, float>::type E;
-      typedef E ev __attribute__((ext_vector_type(2)));
-      const ev mv = __builtin_nontemporal_load(reinterpret_cast<const ev*>(Ab + ((size_t)r * n + k) * n + j));
-      const T ms = {mv.x, mv.y};
-      const double2 m = make_double2((double)ms.x, (double)ms.y);
-      const double2 v = xs[r * n + k];
-      re = fma(m.x, v.x, fma(-m.y, v.y, re));
-      im = fma(m.x, v.y, fma(m.y, v.x, im));
-    }
-  y[(size_t)b * n + j] = make_double2(re, im);
-}
-
 // Fixed-order sums over the workgroup (wavefront shuffles, then the waves in
 // order), valid on thread 0.
 __device__ __forceinline__ void tree2(double& a, double& b) {
@@ -144,84 +111,202 @@ __global__ void __launch_bounds__(CB) caxpby_kernel(long long n, const double2* 
   y[i] = o;
 }
 
-// Device scalars of the coarse CG (one solve at a time).
-enum CgSlot { CS_RR = 0, CS_QQ, CS_ALPHA, CS_STOP, CS_ACTIVE, CS_ITERS, CS_RRN, CS_BETA, CS_FLAG, CS_TMP, CS_N = 16 };
+// ---------------------------------------------------------------------------
+// The coarse CG: A^2 c = A d by CG, three launches an iteration.  An iteration
+// of a small coarse grid is launches more than data (8^3 x 16, 2^4 blocks, 24
+// vectors: 42 MB of stencil; it took eight launches and 86 us, now about 34), so the
+// norms are taken by the matvecs themselves, one partial sum per block, every
+// workgroup that needs a norm adds the partial sums itself (in one order, so all
+// get the same bits), and alpha, beta and the convergence step are part of the
+// vector updates.  The scalars are kept twice: an iteration's last launch reads
+// one set and its first workgroup writes the other.
+// ---------------------------------------------------------------------------
+enum CgSlot { CS_RR = 0, CS_QQ, CS_ALPHA, CS_STOP, CS_ACTIVE, CS_ITERS, CS_GO, CS_BETA, CS_FLAG, CS_N = 16 };
 
-// cs[slot] = sum of the CRED real partials
-__global__ void __launch_bounds__(CB) csum1_kernel(const double* __restrict__ part, double* __restrict__ cs, int slot) {
-  double re = 0, im = 0;
-  for (int i = threadIdx.x; i < CRED; i += CB) re += part[i];
-  tree2(re, im);
-  if (threadIdx.x == 0) cs[slot] = re;
+// Sum of np partial sums, in every thread of the workgroup (one fixed order).
+// Contains two barriers.
+__device__ __forceinline__ double sum_partials(const double* __restrict__ part, int np) {
+  __shared__ double red[2 * (CB / 64)];
+  __shared__ double total;
+  double s = 0, unused = 0;
+  for (int i = threadIdx.x; i < np; i += (int)blockDim.x) s += part[i];
+  block_sum2(s, unused, red);
+  if (threadIdx.x == 0) total = s;
+  __syncthreads();
+  return total;
 }
 
-__global__ void ccg_init_kernel(double* cs, double tol2) {
-  const double bb = cs[CS_RR];
-  cs[CS_STOP] = tol2 * bb;
-  cs[CS_ACTIVE] = (bb > 0 && bb > cs[CS_STOP]) ? 1.0 : 0.0;
-  cs[CS_ITERS] = 0;
-  cs[CS_FLAG] = 0;
-  cs[CS_ALPHA] = 0;
-  cs[CS_BETA] = 0;
+// out[b] = sum of the b-th of gridDim.x equal ranges of np partial sums: beyond
+// FUSED_SUM blocks a norm's partial sums go through this first, where adding all of
+// them in every workgroup would read more than the launch costs (8192 blocks: 64 KB
+// for each of 8192 workgroups, against 148 KB of stencil).
+constexpr int FUSED_SUM = 2048, RANGES = 64;
+__global__ void __launch_bounds__(CB) range_sum_kernel(const double* __restrict__ part, int np, double* __restrict__ out) {
+  const int per = (np + gridDim.x - 1) / gridDim.x;
+  const int k0 = blockIdx.x * per;
+  const double s = sum_partials(part + k0, max(0, min(per, np - k0)));
+  if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
-// alpha = |r|^2 / |A p|^2 while the solve is active, else 0 (the iteration is a no-op)
-__global__ void ccg_alpha_kernel(double* cs) {
-  double a = 0.0;
-  if (cs[CS_ACTIVE] != 0.0) {
-    a = cs[CS_RR] / cs[CS_QQ];
-    if (!(cs[CS_QQ] > 0.0) || !isfinite(a)) {
-      cs[CS_FLAG] = 1.0;
-      cs[CS_ACTIVE] = 0.0;
-      a = 0.0;
+// alpha = |r|^2 / |A p|^2 while the solve is active, else 0 (the iteration is a no-op);
+// go: still active after it
+__device__ __forceinline__ double ccg_alpha(const double* cs, double qq, bool& go, bool& breakdown) {
+  go = cs[CS_ACTIVE] != 0.0;
+  breakdown = false;
+  if (!go) return 0.0;
+  const double a = cs[CS_RR] / qq;
+  if (!(qq > 0.0) || !isfinite(a)) {
+    go = false;
+    breakdown = true;
+    return 0.0;
+  }
+  return a;
+}
+
+enum MatvecMode {
+  MV_PLAIN = 0,  // y = A x
+  MV_NORM = 1,   // y = A x, |y|^2 per block into part_out
+  MV_STEP = 2,   // alpha from part_in and cs, r -= alpha A x (y = r), |r|^2 per block into part_out
+  MV_INIT = 3,   // y = A x, copied to y2, y3 zeroed, |y|^2 per block into part_out
+};
+
+struct MatvecTail {
+  const double* part_in;
+  int np;
+  double* part_out;
+  double* cs;
+  double2 *y2, *y3;
+};
+
+// y[b] = sum_r A[b][r] x[neighbour_r(b)]: one workgroup per block.  A block's
+// stencil is 9 n rows of n contiguous entries, entry j of row (r, k) times x_k of
+// neighbour r adding to y_j; MVT / n rows go through the workgroup at a time, so
+// nearly every lane streams, eight rows in flight, and the lanes' sums for one j are
+// added in order through LDS.  The nine input vectors pass through LDS.  512 blocks
+// of 24 vectors in complex128 (42 MB): 31 -> 19 us against one lane per j and one row
+// at a time, which left 40 of a wave's 64 lanes idle; 8192 blocks of 32 (1.21 GB):
+// 184 us both ways (6.6 TB/s), in complex64 125 -> 93 us.  128 lanes: 256 took 188 us
+// and 64 took 191 us there.
+constexpr int MVT = 128;
+template <class T, int MODE>
+__global__ void __launch_bounds__(MVT) coarse_matvec_kernel(const T* __restrict__ A, const int* __restrict__ bnbr,
+                                                           int n, const double2* __restrict__ x, double2* __restrict__ y,
+                                                           MatvecTail tail) {
+  typedef typename std::conditional<sizeof(T) == 16, double, float>::type E;
+  typedef E ev __attribute__((ext_vector_type(2)));
+  constexpr int U = 8;  // rows in flight per lane
+  __shared__ double2 xs[9 * 64];
+  __shared__ double2 sums[MVT];
+  const int b = blockIdx.x;
+  const int G = MVT / n;  // rows at a time
+  const int g = threadIdx.x / n, j = threadIdx.x - g * n;
+  const int rows = g < G ? 9 * n : 0;  // the lanes left over have none
+  const T* Ab = A + (size_t)b * 9 * n * n + j;
+  ev m[U];
+  auto fetch = [&](int i0) {  // each entry is read once per matvec: non-temporal loads
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + u * G;
+      m[u] = i < rows ? __builtin_nontemporal_load(reinterpret_cast<const ev*>(Ab + (size_t)i * n)) : ev{0, 0};
+    }
+  };
+  fetch(g);  // before the inputs: it needs none of them
+  for (int i = threadIdx.x; i < 9 * n; i += MVT) {
+    const int r = i / n, k = i - r * n;
+    const int src = r < 8 ? bnbr[(size_t)b * 8 + r] : b;
+    xs[i] = x[(size_t)src * n + k];
+  }
+  double alpha = 0;
+  if (MODE == MV_STEP) {
+    bool go, breakdown;
+    const double qq = sum_partials(tail.part_in, tail.np);
+    alpha = ccg_alpha(tail.cs, qq, go, breakdown);
+    if (b == 0 && threadIdx.x == 0) {  // slots no other workgroup of this launch reads
+      tail.cs[CS_ALPHA] = alpha;
+      tail.cs[CS_GO] = go ? 1.0 : 0.0;
+      if (breakdown) tail.cs[CS_FLAG] = 1.0;
     }
   }
-  cs[CS_ALPHA] = a;
-}
-
-// beta = |r_new|^2 / |r|^2; count the iteration; retire once |r_new|^2 <= tol^2 |b'|^2
-__global__ void ccg_beta_kernel(double* cs) {
-  if (cs[CS_ACTIVE] != 0.0) {
-    const double rn = cs[CS_RRN];
-    cs[CS_BETA] = rn / cs[CS_RR];
-    cs[CS_RR] = rn;
-    cs[CS_ITERS] += 1.0;
-    if (!(rn > cs[CS_STOP])) cs[CS_ACTIVE] = 0.0;
-  } else {
-    cs[CS_BETA] = 0.0;
+  __syncthreads();
+  double re = 0, im = 0;
+  for (int i0 = g; i0 < rows; i0 += U * G) {
+    ev w[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) w[u] = m[u];
+    if (i0 + U * G < rows) fetch(i0 + U * G);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + u * G;
+      if (i >= rows) break;
+      const double2 v = xs[i];
+      re = fma((double)w[u].x, v.x, fma(-(double)w[u].y, v.y, re));
+      im = fma((double)w[u].x, v.y, fma((double)w[u].y, v.x, im));
+    }
+  }
+  sums[threadIdx.x] = make_double2(re, im);
+  __syncthreads();
+  double norm = 0, unused = 0;
+  if ((int)threadIdx.x < n) {
+    double2 o = sums[threadIdx.x];
+    for (int k = 1; k < G; ++k) {
+      o.x += sums[threadIdx.x + k * n].x;
+      o.y += sums[threadIdx.x + k * n].y;
+    }
+    const size_t at = (size_t)b * n + threadIdx.x;
+    if (MODE == MV_STEP) {
+      const double2 r = y[at];
+      o = make_double2(r.x - alpha * o.x, r.y - alpha * o.y);
+    }
+    y[at] = o;
+    if (MODE == MV_INIT) {
+      tail.y2[at] = o;
+      tail.y3[at] = make_double2(0.0, 0.0);
+    }
+    norm = fma(o.x, o.x, o.y * o.y);
+  }
+  if (MODE != MV_PLAIN) {
+    __shared__ double red[2 * ((MVT + 63) / 64)];
+    block_sum2(norm, unused, red);
+    if (threadIdx.x == 0) tail.part_out[b] = norm;
   }
 }
 
-// r -= alpha w with the partial sums of |r|^2
-__global__ void __launch_bounds__(CB) caxpy_norm_kernel(long long n, const double2* __restrict__ w,
-                                                        const double* __restrict__ cs, double2* __restrict__ r,
-                                                        double* __restrict__ part) {
-  const double a = cs[CS_ALPHA];
-  double s = 0, dummy = 0;
-  for (long long i = (long long)blockIdx.x * CB + threadIdx.x; i < n; i += (long long)CRED * CB) {
-    const double2 v = w[i];
-    double2 o = r[i];
-    o.x -= a * v.x;
-    o.y -= a * v.y;
-    r[i] = o;
-    s = fma(o.x, o.x, fma(o.y, o.y, s));
-  }
-  tree2(s, dummy);
-  if (threadIdx.x == 0) part[blockIdx.x] = s;
+// |r|^2 of the start, the stopping norm and the state
+__global__ void __launch_bounds__(CB) ccg_init_kernel(const double* __restrict__ part, int np, double* cs, double tol2) {
+  const double bb = sum_partials(part, np);
+  if (threadIdx.x != 0) return;
+  cs[CS_RR] = bb;
+  cs[CS_STOP] = tol2 * bb;
+  cs[CS_ACTIVE] = (bb > 0 && bb > tol2 * bb) ? 1.0 : 0.0;
+  cs[CS_ITERS] = 0;
+  cs[CS_FLAG] = 0;
 }
 
-// c += alpha p; p = r + beta p
+// c += alpha p; p = r + beta p with beta = |r_new|^2 / |r|^2; the first workgroup counts the
+// iteration and retires the solve once |r_new|^2 <= tol^2 |b'|^2 (state read from cs, written
+// to next)
 __global__ void __launch_bounds__(CB) ccg_xp_kernel(long long n, double2* __restrict__ c, double2* __restrict__ p,
-                                                    const double2* __restrict__ r, const double* __restrict__ cs) {
+                                                    const double2* __restrict__ r, const double* __restrict__ part,
+                                                    int np, const double* __restrict__ cs, double* __restrict__ next) {
+  const double rn = sum_partials(part, np);
+  const bool go = cs[CS_GO] != 0.0;
+  const double a = cs[CS_ALPHA], b = go ? rn / cs[CS_RR] : 0.0;
   const long long i = (long long)blockIdx.x * CB + threadIdx.x;
-  if (i >= n) return;
-  const double a = cs[CS_ALPHA], b = cs[CS_BETA];
-  const double2 pv = p[i], rv = r[i];
-  double2 cv = c[i];
-  cv.x += a * pv.x;
-  cv.y += a * pv.y;
-  c[i] = cv;
-  p[i] = make_double2(rv.x + b * pv.x, rv.y + b * pv.y);
+  if (i < n) {
+    const double2 pv = p[i], rv = r[i];
+    double2 cv = c[i];
+    cv.x += a * pv.x;
+    cv.y += a * pv.y;
+    c[i] = cv;
+    p[i] = make_double2(rv.x + b * pv.x, rv.y + b * pv.y);
+  }
+  if (i == 0) {
+    next[CS_STOP] = cs[CS_STOP];
+    next[CS_FLAG] = cs[CS_FLAG];
+    next[CS_RR] = go ? rn : cs[CS_RR];
+    next[CS_ITERS] = cs[CS_ITERS] + (go ? 1.0 : 0.0);
+    next[CS_ACTIVE] = go && rn > cs[CS_STOP] ? 1.0 : 0.0;
+  }
 }
 
 unsigned blocks_for(long long n) { return (unsigned)((n + CB - 1) / CB); }
@@ -238,8 +323,9 @@ struct dwf_hdcr_s {
   dwf_hdcr_params prm;
   const char* basis;   // caller's basis (packed both layout, nvec fields), set by dwf_hdcr_set_basis
   void* A;             // [nb][9][n][n], complex128 or complex64 (prm.coarse_prec)
-  double2* cv[7];      // coarse vectors: d, c, r, p, q, w, b'
-  double* part;        // [2][CRED] partials, 2 result doubles, then the coarse CG's CS_N scalars
+  double2* cv[5];      // coarse vectors: d, c, r, p, q
+  double* part;        // [2][CRED] partials, 2 result doubles
+  double* ccg;         // coarse CG: two sets of CS_N scalars, two of nb partial sums, RANGES range sums
   char* work;          // 9 both fields
   char* gb;            // GCR source Gamma_5 eta
   char* gr;            // GCR residual
@@ -277,8 +363,9 @@ size_t carve_hdcr(dwf_hdcr_s* d, const dwf_context* h, int nvec, int nk, char* b
   dwf_hdcr_s tmp;
   dwf_hdcr_s* x = d ? d : &tmp;
   x->A = take((size_t)h->nb * 9 * nvec * nvec * 16);  // sized for complex128
-  for (int i = 0; i < 7; ++i) x->cv[i] = reinterpret_cast<double2*>(take(cvb));
-  x->part = reinterpret_cast<double*>(take((2 * CRED + 2 + CS_N) * sizeof(double)));
+  for (int i = 0; i < 5; ++i) x->cv[i] = reinterpret_cast<double2*>(take(cvb));
+  x->part = reinterpret_cast<double*>(take((2 * CRED + 2) * sizeof(double)));
+  x->ccg = reinterpret_cast<double*>(take((2 * CS_N + 2 * (size_t)h->nb + RANGES) * sizeof(double)));
   x->work = take(9 * 2 * fb);
   x->gb = take(2 * fb);
   x->gr = take(2 * fb);
@@ -417,13 +504,14 @@ int smoother(dwf_hdcr_s* hd, const char* r, char* out) {
   return DWF_OK;
 }
 
-hipError_t coarse_matvec(dwf_hdcr_s* hd, const double2* x, double2* y) {
+template <int MODE>
+hipError_t coarse_matvec(dwf_hdcr_s* hd, const double2* x, double2* y, const MatvecTail& tail) {
   if (hd->prm.coarse_prec == DWF_F32)
-    hipLaunchKernelGGL(coarse_matvec_kernel<float2>, dim3(hd->nb), dim3(64), 0, hd->h->stream,
-                       reinterpret_cast<const float2*>(hd->A), hd->h->bnbr, hd->nvec, x, y);
+    hipLaunchKernelGGL((coarse_matvec_kernel<float2, MODE>), dim3(hd->nb), dim3(MVT), 0, hd->h->stream,
+                       reinterpret_cast<const float2*>(hd->A), hd->h->bnbr, hd->nvec, x, y, tail);
   else
-    hipLaunchKernelGGL(coarse_matvec_kernel<double2>, dim3(hd->nb), dim3(64), 0, hd->h->stream,
-                       reinterpret_cast<const double2*>(hd->A), hd->h->bnbr, hd->nvec, x, y);
+    hipLaunchKernelGGL((coarse_matvec_kernel<double2, MODE>), dim3(hd->nb), dim3(MVT), 0, hd->h->stream,
+                       reinterpret_cast<const double2*>(hd->A), hd->h->bnbr, hd->nvec, x, y, tail);
   return hipGetLastError();
 }
 
@@ -436,22 +524,35 @@ constexpr int CG_BATCH = 8;
 int coarse_cgnr(dwf_hdcr_s* hd, const double2* d, double2* cvec, double tol, int maxiter, int* iters) {
   dwf_context* c = hd->h;
   const long long n = coarse_len(hd);
-  double2 *r = hd->cv[2], *p = hd->cv[3], *q = hd->cv[4], *w = hd->cv[5], *bp = hd->cv[6];
-  double* cs = hd->part + 2 * CRED + 2;
-  auto norm_into = [&](const double2* v, int slot) {
-    hipLaunchKernelGGL(cdot_kernel, dim3(CRED), dim3(CB), 0, c->stream, n, v, v, hd->part);
-    hipLaunchKernelGGL(csum1_kernel, dim3(1), dim3(CB), 0, c->stream, hd->part, cs, slot);
+  double2 *r = hd->cv[2], *p = hd->cv[3], *q = hd->cv[4];
+  double* state[2] = {hd->ccg, hd->ccg + CS_N};
+  double* pq = hd->ccg + 2 * CS_N;  // per block: |q|^2, then |r|^2
+  double* pr = pq + hd->nb;
+  double* ranges = pr + hd->nb;
+  // the partial sums as their readers take them
+  auto reduced = [&](const double* part, const double** out, int* np) -> hipError_t {
+    *out = part;
+    *np = hd->nb;
+    if (hd->nb <= FUSED_SUM) return hipSuccess;
+    hipLaunchKernelGGL(range_sum_kernel, dim3(RANGES), dim3(CB), 0, c->stream, part, hd->nb, ranges);
+    *out = ranges;
+    *np = RANGES;
+    return hipGetLastError();
   };
-  HIP_TRY(coarse_matvec(hd, d, bp));
-  HIP_TRY(caxpby(hd, n, nullptr, 0, 0, 0, cvec));
-  HIP_TRY(caxpby(hd, n, bp, 1, 0, 0, r));
-  HIP_TRY(caxpby(hd, n, bp, 1, 0, 0, p));
-  norm_into(r, CS_RR);
-  hipLaunchKernelGGL(ccg_init_kernel, dim3(1), dim3(1), 0, c->stream, cs, tol * tol);
+  const double* part = nullptr;
+  int np = 0;
+  MatvecTail t{};
+  t.part_out = pr;
+  t.y2 = p;
+  t.y3 = cvec;
+  HIP_TRY(coarse_matvec<MV_INIT>(hd, d, r, t));  // r = p = A d, c = 0
+  HIP_TRY(reduced(pr, &part, &np));
+  hipLaunchKernelGGL(ccg_init_kernel, dim3(1), dim3(CB), 0, c->stream, part, np, state[0], tol * tol);
   HIP_TRY(hipGetLastError());
+  int cur = 0;  // the state the next iteration reads
   double st[CS_N];
   auto read_state = [&]() -> int {
-    HIP_TRY(hipMemcpyAsync(st, cs, sizeof st, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(hipMemcpyAsync(st, state[cur], sizeof st, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
     return DWF_OK;
   };
@@ -462,15 +563,18 @@ int coarse_cgnr(dwf_hdcr_s* hd, const double2* d, double2* cvec, double tol, int
     const int batch = std::min(batch_size, maxiter - done);
     const double rr_before = st[CS_RR];
     for (int k = 0; k < batch; ++k) {
-      HIP_TRY(coarse_matvec(hd, p, q));                       // q = A p
-      norm_into(q, CS_QQ);                                    // |q|^2 = p.A^2 p
-      hipLaunchKernelGGL(ccg_alpha_kernel, dim3(1), dim3(1), 0, c->stream, cs);
-      HIP_TRY(coarse_matvec(hd, q, w));                       // w = A^2 p
-      hipLaunchKernelGGL(caxpy_norm_kernel, dim3(CRED), dim3(CB), 0, c->stream, n, w, cs, r, hd->part);
-      hipLaunchKernelGGL(csum1_kernel, dim3(1), dim3(CB), 0, c->stream, hd->part, cs, (int)CS_RRN);
-      hipLaunchKernelGGL(ccg_beta_kernel, dim3(1), dim3(1), 0, c->stream, cs);
-      hipLaunchKernelGGL(ccg_xp_kernel, dim3(gb), dim3(CB), 0, c->stream, n, cvec, p, r, cs);
+      MatvecTail tq{}, tr{};
+      tq.part_out = pq;
+      HIP_TRY(coarse_matvec<MV_NORM>(hd, p, q, tq));  // q = A p, |q|^2 = p.A^2 p
+      HIP_TRY(reduced(pq, &tr.part_in, &tr.np));
+      tr.part_out = pr;
+      tr.cs = state[cur];
+      HIP_TRY(coarse_matvec<MV_STEP>(hd, q, r, tr));  // alpha; r -= alpha A q, |r|^2
+      HIP_TRY(reduced(pr, &part, &np));
+      hipLaunchKernelGGL(ccg_xp_kernel, dim3(gb), dim3(CB), 0, c->stream, n, cvec, p, r, part, np, state[cur],
+                         state[cur ^ 1]);
       HIP_TRY(hipGetLastError());
+      cur ^= 1;
     }
     done += batch;
     if (int rc = read_state()) return rc;
@@ -635,7 +739,7 @@ const void* dwf_hdcr_coarse_data(dwf_hdcr hd) { return hd ? hd->A : nullptr; }
 int dwf_hdcr_coarse_apply(dwf_hdcr hd, const void* x, void* y) {
   if (int r = check_hd(hd, true)) return r;
   if (!x || !y || x == y) return fail(DWF_EINVAL, "dwf_hdcr_coarse_apply: x and y must be distinct");
-  HIP_TRY(coarse_matvec(hd, reinterpret_cast<const double2*>(x), reinterpret_cast<double2*>(y)));
+  HIP_TRY(coarse_matvec<MV_PLAIN>(hd, reinterpret_cast<const double2*>(x), reinterpret_cast<double2*>(y), MatvecTail{}));
   return DWF_OK;
 }
 

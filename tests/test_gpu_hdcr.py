@@ -389,3 +389,59 @@ def test_stencil_shapes_match_oracle(dims, Ls, block, nvec):
     hd32 = dwf.HDCR(op, nvec, nkrylov=1, coarse_prec=1)
     hd32.set_basis(basis)
     assert np.array_equal(host(hd32.coarse_operator()), S.astype(np.complex64))  # the same sums, rounded once
+
+
+@pytest.mark.parametrize(
+    "dims, Ls, nvec, prec",
+    [
+        ((4, 4, 4, 4), 2, 1, 0),  # more rows at a time (256) than a block has (9)
+        ((4, 4, 4, 8), 2, 3, 1),  # 27 rows, 85 at a time
+        ((4, 4, 4, 4), 4, 37, 0),  # six rows at a time, 34 lanes left over
+        ((4, 4, 4, 4), 4, 64, 1),  # four rows at a time, the most there are
+        ((16, 16, 16, 16), 2, 2, 0),  # 4096 blocks: the norms' partial sums are reduced by ranges first
+    ],
+)
+def test_coarse_matvec_and_cg_shapes(dims, Ls, nvec, prec):
+    """The stencil matvec entry by entry, and the first iterates of the coarse CG."""
+    import paper_2103_05034_amd as dwf
+
+    block = (2, 2, 2, 2)
+    op, _ = make_operator(dims, Ls, prec=F64, max_nrhs=1, max_cg_rhs=2)
+    nb = op.set_blocks(block, both=True)
+    basis = pack(op, synth.gaussian_fermion_batch(dims, Ls, nvec, 51), BOTH)
+    op.block_orthonormalize(basis, nvec)
+    hd = dwf.HDCR(op, nvec, nkrylov=1, coarse_prec=prec)
+    hd.set_basis(basis)
+    S = host(hd.coarse_operator()).astype(np.complex128)  # [nb, 9, k, j]
+    coords, ng = block_coords(dims, block)
+    nbr = np.empty((nb, 9), dtype=int)
+    for b, c in enumerate(coords):
+        for d in range(9):
+            cc = list(c)
+            if d < 8:
+                cc[d // 2] = (cc[d // 2] + (ng[d // 2] - 1 if d % 2 else 1)) % ng[d // 2]
+            nbr[b, d] = block_index(cc, ng)
+
+    def apply(x):
+        return np.einsum("bdkj,bdk->bj", S, x[nbr])
+
+    rng = np.random.default_rng(52)
+    x = rng.standard_normal((nb, nvec)) + 1j * rng.standard_normal((nb, nvec))
+    got = host(hd.coarse_apply(dev_tensor(x)))
+    # 9 n complex products, each sum rounding at most 2 * 9 n times
+    bound = 4 * 9 * nvec * 2.0**-53 * np.einsum("bdkj,bdk->bj", np.abs(S), np.abs(x[nbr]))
+    assert np.all(np.abs(got - apply(x)) <= bound)
+    # the first iterates of CG on A^2 c = A x against the same recursion here: each iteration adds a few
+    # roundings of the size of the iterate, and twenty steps let none of them grow by 1e4
+    c, it = hd.coarse_solve(dev_tensor(x), tol=1e-14, maxiter=20)
+    r = apply(x)
+    p, want, rr = r.copy(), np.zeros_like(r), np.vdot(r, r).real
+    for _ in range(20):
+        q = apply(p)
+        alpha = rr / np.vdot(q, q).real
+        want += alpha * p
+        r = r - alpha * apply(q)
+        new = np.vdot(r, r).real
+        p, rr = r + new / rr * p, new
+    assert it == 20
+    assert np.linalg.norm(host(c) - want) < 20 * 1e4 * 2.0**-53 * 9 * nvec * np.linalg.norm(want)
