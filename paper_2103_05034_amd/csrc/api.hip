@@ -415,14 +415,14 @@ int dwf_ddw(dwf_handle h, const void* in, void* out, int nrhs, int dagger) {
   const size_t half = fbytes(h, h->prec) * nrhs;
   const char* in_c = reinterpret_cast<const char*>(in);
   char* out_c = reinterpret_cast<char*>(out);
+  HopArgs a[2] = {};
   for (int p = 0; p < 2; ++p) {
-    HopArgs a{};
-    a.in = in_c + (1 - p) * half;
-    a.x = in_c + p * half;
-    a.out = out_c + p * half;
-    a.alpha = -0.5;
-    HIP_TRY(launch_hop(h, h->prec, a, p, dagger ? 1 : 0, EPI_M5, nrhs));
+    a[p].in = in_c + (1 - p) * half;
+    a[p].x = in_c + p * half;
+    a[p].out = out_c + p * half;
+    a[p].alpha = -0.5;
   }
+  HIP_TRY(launch_hop_both(h, h->prec, a[0], a[1], dagger ? 1 : 0, EPI_M5, nrhs));
   return DWF_OK;
 }
 

@@ -394,6 +394,9 @@ enum Epilogue {
   EPI_CGR = 4,    // q = M5D x + alpha * Dhop(in) kept in registers; out -= alpha_cg * q  (CG residual, FP64/FP32)
 };
 
+// order of the parities in a hop launch over both
+enum { HOP_ONE = 0, HOP_FASTEST = 1, HOP_SLOWEST = 2 };
+
 struct HopArgs {
   const char* in;     // other parity, rhs stride in_stride
   char* out;          // out parity
@@ -422,6 +425,15 @@ struct HopArgs {
   const double* scal; // EPI_CGR: per-rhs solver scalars, alpha_cg = scal[rhs * NSCAL + S_ALPHA]
   int x_after;        // EPI_M5INV: add beta * x after the inverse instead of before
   float one;          // 1.0, passed at run time (keeps the FP16 projection FMAs as mixed-precision FMAs)
+  int both;           // HOP_ONE: one output parity; else both, `odd` holding the odd one's pointers
+  struct {
+    const char* in;
+    char* out;
+    const char *x, *y, *z, *w;
+    const void* links;
+    const int* nbr;
+    const int* order;
+  } odd;
 };
 
 // ---------------------------------------------------------------------------

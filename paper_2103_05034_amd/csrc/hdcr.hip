@@ -409,18 +409,16 @@ int cnorm2(dwf_hdcr_s* hd, long long n, const void* x, double& nn) {
   return cdot(hd, n, x, x, nn, im);
 }
 
-// out = D_DW in (dag = 0) or D_DW^dag in: one hop launch per output parity
+// out = D_DW in (dag = 0) or D_DW^dag in
 hipError_t ddw1(dwf_context* c, BF in, BFm out, int dag) {
+  HopArgs a[2] = {};
   for (int p = 0; p < 2; ++p) {
-    HopArgs a{};
-    a.in = p ? in.e : in.o;
-    a.x = p ? in.o : in.e;
-    a.out = p ? out.o : out.e;
-    a.alpha = -0.5;
-    hipError_t e = launch_hop(c, DWF_F64, a, p, dag, EPI_M5, 1);
-    if (e != hipSuccess) return e;
+    a[p].in = p ? in.e : in.o;
+    a[p].x = p ? in.o : in.e;
+    a[p].out = p ? out.o : out.e;
+    a[p].alpha = -0.5;
   }
-  return hipSuccess;
+  return launch_hop_both(c, DWF_F64, a[0], a[1], dag, EPI_M5, 1);
 }
 
 // out = ca D^dag D in + cb y + cc z + cw w (out may alias z or w); tmp = D in
@@ -428,23 +426,21 @@ hipError_t ddagd_step(dwf_context* c, BF in, BFm out, BF y, BF z, double ca, dou
                       BFm tmp) {
   hipError_t e = ddw1(c, in, tmp, 0);
   if (e != hipSuccess) return e;
+  HopArgs b[2] = {};
   for (int p = 0; p < 2; ++p) {
-    HopArgs b{};
-    b.in = p ? tmp.e : tmp.o;
-    b.x = p ? tmp.o : tmp.e;
-    b.y = p ? y.o : y.e;
-    b.z = p ? z.o : z.e;
-    b.w = w.e ? (p ? w.o : w.e) : nullptr;
-    b.out = p ? out.o : out.e;
-    b.alpha = -0.5;
-    b.ca = ca;
-    b.cb = cb;
-    b.cc = cc;
-    b.cw = cw;
-    e = launch_hop(c, DWF_F64, b, p, 1, EPI_CHEB, 1);
-    if (e != hipSuccess) return e;
+    b[p].in = p ? tmp.e : tmp.o;
+    b[p].x = p ? tmp.o : tmp.e;
+    b[p].y = p ? y.o : y.e;
+    b[p].z = p ? z.o : z.e;
+    b[p].w = w.e ? (p ? w.o : w.e) : nullptr;
+    b[p].out = p ? out.o : out.e;
+    b[p].alpha = -0.5;
+    b[p].ca = ca;
+    b[p].cb = cb;
+    b[p].cc = cc;
+    b[p].cw = cw;
   }
-  return hipSuccess;
+  return launch_hop_both(c, DWF_F64, b[0], b[1], 1, EPI_CHEB, 1);
 }
 
 hipError_t g5_combine(dwf_hdcr_s* hd, const char* a, const char* b, double cb, char* out) {

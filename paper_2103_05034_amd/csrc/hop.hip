@@ -279,7 +279,22 @@ hop_kernel(HopArgs a) {
   cplx<R>* ll = reinterpret_cast<cplx<R>*>(smem_raw);  // links [72][spb], kept for all rhs of the workgroup
   char* scratch = smem_raw + (size_t)spb * 72 * sizeof(cplx<R>);  // M5D^{-1} columns, x, reduction
   const int b = blockIdx.x;
-  const int logical = (b & 7) * a.nb8 + (b >> 3);
+  int logical = (b & 7) * a.nb8 + (b >> 3);
+  if (a.both != HOP_ONE) {  // both output parities in one launch (launch_hop_both)
+    const bool odd = a.both == HOP_FASTEST ? (logical & 1) : (b >> 3) >= a.nb8;
+    logical = a.both == HOP_FASTEST ? logical >> 1 : odd ? logical - a.nb8 : logical;
+    if (odd) {
+      a.in = a.odd.in;
+      a.out = a.odd.out;
+      a.x = a.odd.x;
+      a.y = a.odd.y;
+      a.z = a.odd.z;
+      a.w = a.odd.w;
+      a.links = a.odd.links;
+      a.nbr = a.odd.nbr;
+      a.order = a.odd.order;
+    }
+  }
   if (logical >= a.nblocks) return;  // whole workgroup leaves together
   const int tid = threadIdx.x;
   const int sl = tid / Ls;
@@ -582,7 +597,7 @@ void fill_shape(const dwf_context* ctx, HopArgs& a) {
 
 template <int PREC, int PIN, int PX, bool DAG, int EPI, int DEPTH>
 static hipError_t launch_hop_t(const HopArgs& a, int nrhs, hipStream_t st) {
-  dim3 grid(a.nb8 * 8, (nrhs + a.rpb - 1) / a.rpb);
+  dim3 grid(a.nb8 * (a.both == HOP_SLOWEST ? 16 : 8), (nrhs + a.rpb - 1) / a.rpb);
   dim3 block(a.spb * a.Ls);
   const size_t lds = std::max(hop_lds(PREC, a.spb, a.Ls, EPI, a.partial != nullptr), (size_t)a.lds_floor);
   if (a.rpb > 1)
@@ -633,21 +648,23 @@ static hipError_t launch_hop_mixed(const HopArgs& a, int pin, int px, int dag, i
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_hop_ex(dwf_context* ctx, int prec, int pin, int px, HopArgs a, int out_parity, int dag, int epi,
-                         int nrhs) {
-  if (prec != DWF_F64 && ctx->links32 == nullptr) return hipErrorInvalidValue;  // FP64 handles hold no FP32 links
-  fill_shape(ctx, a);
+// links, neighbour table and traversal order of an output parity
+static void parity_tables(const dwf_context* ctx, int prec, int out_parity, const void** links, const int** nbr,
+                          const int** order) {
   const long long V4h = ctx->g.V4h;
-  a.nbr = ctx->nbr + (size_t)out_parity * 8 * V4h;
+  *nbr = ctx->nbr + (size_t)out_parity * 8 * V4h;
   const size_t link_elems = (size_t)out_parity * 8 * 9 * V4h;
   if (prec == DWF_F64)
-    a.links = reinterpret_cast<const double2*>(ctx->links64) + link_elems;
+    *links = reinterpret_cast<const double2*>(ctx->links64) + link_elems;
   else
-    a.links = reinterpret_cast<const float2*>(ctx->links32) + link_elems;
+    *links = reinterpret_cast<const float2*>(ctx->links32) + link_elems;
+  *order = ctx->order_mode ? ctx->order + (size_t)out_parity * V4h : nullptr;
+}
+
+static hipError_t launch_filled(dwf_context* ctx, int prec, int pin, int px, HopArgs& a, int dag, int epi, int nrhs) {
   a.stride = field_bytes_rhs(ctx, prec);
   a.in_stride = field_bytes_rhs(ctx, pin);
   a.x_stride = field_bytes_rhs(ctx, px);
-  a.order = ctx->order_mode ? ctx->order + (size_t)out_parity * V4h : nullptr;
   a.lds_floor = ctx->lds_floor;
   a.one = 1.0f;
   a.nrhs = nrhs;
@@ -666,6 +683,36 @@ hipError_t launch_hop_ex(dwf_context* ctx, int prec, int pin, int px, HopArgs a,
   }
   timing_end(ctx);
   return e;
+}
+
+hipError_t launch_hop_ex(dwf_context* ctx, int prec, int pin, int px, HopArgs a, int out_parity, int dag, int epi,
+                         int nrhs) {
+  if (prec != DWF_F64 && ctx->links32 == nullptr) return hipErrorInvalidValue;  // FP64 handles hold no FP32 links
+  fill_shape(ctx, a);
+  parity_tables(ctx, prec, out_parity, &a.links, &a.nbr, &a.order);
+  return launch_filled(ctx, prec, pin, px, a, dag, epi, nrhs);
+}
+
+// Both output parities of D_DW in one launch: the even outputs' fields from `even`, the odd ones'
+// from `odd`.  A hop on a small lattice is bound by its launch, its fill and its drain, which two
+// parities then share: 16^3 x 16 Ls 16 FP64 178 -> 165 us, 8^3 x 16 Ls 16 32.0 -> 25.3 us, 4^4
+// Ls 8 16.3 -> 10.8 us (D_DW, back to back).  On a large one the order decides what the 4 MiB L2
+// of an XCD holds.  With the parity fastest, two neighbouring workgroups share the spinors that
+// one reads as neighbours and the other as its own: FP32 16^3 x 32 Ls 16 158 -> 143 us (parity
+// slowest 152), 24^3 x 48 Ls 24 1487 -> 1412 us (1474).  In FP64 the spinors of one parity alone
+// exceed L2 and interleaving two costs more neighbour reuse than it gains: 16^3 x 32 339 us as two
+// launches, 342 with the parity fastest, 326 with it slowest (each XCD its even then its odd
+// sites); 24^3 x 48 Ls 12 1624, 1596, 1620.  So FP64 takes the parity slowest, FP32 and FP16S
+// fastest; neither is behind the two launches at any size measured.
+hipError_t launch_hop_both(dwf_context* ctx, int prec, HopArgs even, const HopArgs& odd, int dag, int epi, int nrhs) {
+  if (prec != DWF_F64 && ctx->links32 == nullptr) return hipErrorInvalidValue;
+  fill_shape(ctx, even);
+  even.both = prec == DWF_F64 ? HOP_SLOWEST : HOP_FASTEST;
+  if (even.both == HOP_FASTEST) even.nb8 = (2 * even.nblocks + 7) / 8;
+  parity_tables(ctx, prec, DWF_EVEN, &even.links, &even.nbr, &even.order);
+  even.odd = {odd.in, odd.out, odd.x, odd.y, odd.z, odd.w, nullptr, nullptr, nullptr};
+  parity_tables(ctx, prec, DWF_ODD, &even.odd.links, &even.odd.nbr, &even.odd.order);
+  return launch_filled(ctx, prec, prec, prec, even, dag, epi, nrhs);
 }
 
 hipError_t launch_hop(dwf_context* ctx, int prec, HopArgs a, int out_parity, int dag, int epi, int nrhs) {

@@ -33,6 +33,8 @@ hipError_t launch_hop(dwf_context* ctx, int prec, HopArgs a, int out_parity, int
 // out (EPI_M5)
 hipError_t launch_hop_ex(dwf_context* ctx, int prec, int pin, int px, HopArgs a, int out_parity, int dag, int epi,
                          int nrhs);
+// one launch for the two output parities (their pointers from `even` and `odd`, the rest from `even`)
+hipError_t launch_hop_both(dwf_context* ctx, int prec, HopArgs even, const HopArgs& odd, int dag, int epi, int nrhs);
 hipError_t launch_site5(dwf_context* ctx, int prec, const char* in, char* out, int dag, int inv, int nrhs);
 
 // setup.hip

@@ -127,6 +127,23 @@ def test_ddw_f64(dims, Ls, dagger):
     assert rel(got, L.ddw(U, nat[0], M5, MF, dag=dagger)) < 1e-13
 
 
+@pytest.mark.parametrize("prec,tol", [(F64, 1e-13), (F32, 1e-6), (F16S, 2e-3)])
+@pytest.mark.parametrize("dims,Ls,spb", [((2, 2, 2, 2), 4, 1), ((4, 4, 6, 8), 5, 7), ((6, 4, 2, 4), 12, 5), ((4, 4, 4, 4), 8, 16)])
+def test_ddw_both_parities_in_one_launch(dims, Ls, spb, prec, tol):
+    """The two parities' workgroups share a launch: tile counts that do and do not divide into the
+    8 XCDs, ragged last tiles and several right-hand sides, against the oracle on the stored input."""
+    nrhs = 3
+    op, U = make_operator(dims, Ls, eps=0.5, seed=47, prec=prec)
+    op.set_tile(spb)
+    inp = pack(op, fields(dims, Ls, nrhs, seed=48), BOTH)
+    src = unpack(op, inp, nrhs, BOTH)
+    out = op.new_field(nrhs, both=True)
+    for dagger in (False, True):
+        op.ddw(inp, out, nrhs, dagger)
+        exp = np.stack([L.ddw(U, v, M5, MF, dag=dagger) for v in src])
+        assert rel_per_rhs(unpack(op, out, nrhs, BOTH), exp) < tol
+
+
 @pytest.mark.parametrize("dims,Ls", SHAPES)
 def test_mpc_and_normal_operator_f64(dims, Ls):
     nrhs = 2
