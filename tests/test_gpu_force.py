@@ -109,3 +109,22 @@ def test_lie_force(dims, Ls):
     assert Fg.shape == U.shape[:5] + (8,)
     assert rel(Fg, F.lie_force(U, G.cpu().numpy())) < 1e-14
     assert rel(Fg, F.lie_force(U, F.link_gradient(U, X, Y, M5, MF))) < 1e-13
+
+
+@pytest.mark.parametrize("dims", [(2, 2, 2, 6), (2, 2, 2, 10), (2, 2, 6, 6)])
+def test_lie_force_ragged_workgroups(dims):
+    """Link counts (192, 320, 576) that leave the last 256-link workgroup partly empty, with an
+    output that is aligned to a double only and guarded on both sides."""
+    import torch
+
+    op, U = make_operator(dims, 4, eps=0.5, seed=39)
+    rng = np.random.default_rng(40)
+    G = rng.standard_normal(U.shape) + 1j * rng.standard_normal(U.shape)
+    Ud, Gd = torch.from_numpy(U).cuda(), torch.from_numpy(G).cuda()
+    n = U.size // 9 * 8
+    buf = torch.full((n + 2,), 7.0, dtype=torch.float64, device="cuda")
+    op.lie_force(Ud, Gd, buf[1 : n + 1].view(U.shape[:5] + (8,)))
+    torch.cuda.synchronize()
+    got = buf.cpu().numpy()
+    assert got[0] == 7.0 and got[-1] == 7.0
+    assert rel(got[1:-1].reshape(U.shape[:5] + (8,)), F.lie_force(U, G)) < 1e-14
