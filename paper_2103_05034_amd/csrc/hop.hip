@@ -572,13 +572,26 @@ static size_t hop_lds(int prec, int spb, int Ls, int epi, bool reduce) {
   return (size_t)spb * 72 * cplx_bytes(prec) + scratch;
 }
 
+// Sites of a workgroup where the caller has chosen none, for a parity of `points` (site, s) pairs.
+// Up to 4 waves for each of the 1024 SIMDs every wave runs at once and the launch lasts as long as
+// its fullest CU: workgroups of one wave spread most evenly and none waits for another at a
+// barrier.  M_pc^dag M_pc with 64 against 256 lanes: FP64 4^4 Ls 8 31.5 and 36.9 us, 8^3 x 16
+// Ls 12 48.1 and 53.5, 12^3 x 24 Ls 10 151 and 172; FP32 27.2 and 29.0, 32.4 and 33.8, 76 and 84.
+// A wave that Ls does not fill to 7/8 gives that back (8^3 x 16 Ls 48: 148 and 145), so the
+// smallest workgroup that it does fill is taken (192 lanes: 138).  Above that size the wide
+// workgroup is as good or better (16^3 x 32 Ls 16 FP64 663 and 653, 24^3 x 48 Ls 12 3136 and 2992).
+static int default_tile(long long points, int Ls) {
+  int lanes = 256;
+  if (points <= 4 * 64 * 1024)
+    for (int l = 192; l >= 64; l -= 64)
+      if (l / Ls * Ls * 8 >= l * 7) lanes = l;
+  return std::min(lanes / Ls, 64);
+}
+
 void fill_shape(const dwf_context* ctx, HopArgs& a) {
   const int Ls = ctx->g.Ls;
   int spb = ctx->spb;
-  if (spb <= 0) {
-    spb = 256 / Ls;
-    if (spb > 64) spb = 64;
-  }
+  if (spb <= 0) spb = default_tile(ctx->g.V4h * Ls, Ls);
   if (spb * Ls > 256) spb = 256 / Ls;
   if (spb < 1) spb = 1;
   // every staging buffer must fit 64 KiB of LDS

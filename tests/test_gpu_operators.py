@@ -144,6 +144,24 @@ def test_ddw_both_parities_in_one_launch(dims, Ls, spb, prec, tol):
         assert rel_per_rhs(unpack(op, out, nrhs, BOTH), exp) < tol
 
 
+@pytest.mark.parametrize("prec", [F64, F32, F16S])
+@pytest.mark.parametrize("Ls", [1, 5, 24, 33, 48, 64, 96])
+def test_default_tile_matches_widest(Ls, prec):
+    """The default workgroup of a small lattice (one to four waves, by how full Ls leaves them)
+    gives bitwise the fields of the widest one, which the parity tests above pin."""
+    dims, nrhs = (4, 2, 4, 6), 2
+    op, _ = make_operator(dims, Ls, eps=0.5, seed=49, prec=prec)
+    inp = pack(op, fields(dims, Ls, nrhs, seed=50), BOTH)
+    got = []
+    for spb in (0, max(1, min(256 // Ls, 64))):
+        op.set_tile(spb)
+        pc, full = op.new_field(nrhs), op.new_field(nrhs, both=True)
+        op.mpcdagmpc(inp, pc, nrhs)
+        op.ddw(inp, full, nrhs, True)
+        got.append((pc.cpu(), full.cpu()))
+    assert all((a == b).all() for a, b in zip(*got))
+
+
 @pytest.mark.parametrize("dims,Ls", SHAPES)
 def test_mpc_and_normal_operator_f64(dims, Ls):
     nrhs = 2
