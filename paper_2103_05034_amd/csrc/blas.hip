@@ -320,6 +320,122 @@ __global__ void cg_flush_kernel(VecGeom g, char* x, DirSet d, const char* r, cha
   store_once<PP>(pn + rhs * sp, g, i, vr);
 }
 
+// The two updates above for FP64 and FP32 directions, a lane per pair of components 2j, 2j + 1 of
+// a (site, s) instead of per spinor, with the same fma per number: on a small lattice a lane per
+// spinor leaves most of the chip's load queues idle (8^3 x 16 Ls 12: 192 workgroups; direction
+// 8.6 -> 6.9 us, flush of four 20.4 -> 15.9 us), on a large one both run at 6.3 TB/s (16^3 x 32
+// Ls 16: 92 and 265 us).  FP16 + scale needs the spinor's largest number and stays with the above.
+typedef double d2v __attribute__((ext_vector_type(2)));
+typedef float f4v __attribute__((ext_vector_type(4)));
+
+template <bool NT, class V>
+__device__ __forceinline__ V pair_load(const V* q) {
+  if constexpr (NT) return __builtin_nontemporal_load(q);
+  return *q;
+}
+template <bool NT, class V>
+__device__ __forceinline__ void pair_store(V v, V* q) {
+  if constexpr (NT)
+    __builtin_nontemporal_store(v, q);
+  else
+    *q = v;
+}
+
+template <int P, bool NT>
+struct PairOf;  // 16 bytes of an FP32 field, twice 16 bytes at a distance of Ls of an FP64 one
+
+template <bool NT>
+struct PairOf<DWF_F64, NT> {
+  static __device__ __forceinline__ void load(const char* f, long long row, int s, int Ls, double v[4]) {
+    const d2v* q = reinterpret_cast<const d2v*>(f) + 2 * row * Ls + s;
+    const d2v a = pair_load<NT>(q), b = pair_load<NT>(q + Ls);
+    v[0] = a.x, v[1] = a.y, v[2] = b.x, v[3] = b.y;
+  }
+  static __device__ __forceinline__ void store(char* f, long long row, int s, int Ls, const double v[4]) {
+    d2v* q = reinterpret_cast<d2v*>(f) + 2 * row * Ls + s;
+    pair_store<NT>(d2v{v[0], v[1]}, q);
+    pair_store<NT>(d2v{v[2], v[3]}, q + Ls);
+  }
+};
+template <bool NT>
+struct PairOf<DWF_F32, NT> {
+  static __device__ __forceinline__ void load(const char* f, long long row, int s, int Ls, double v[4]) {
+    const f4v a = pair_load<NT>(reinterpret_cast<const f4v*>(f) + row * Ls + s);
+    v[0] = a.x, v[1] = a.y, v[2] = a.z, v[3] = a.w;
+  }
+  static __device__ __forceinline__ void store(char* f, long long row, int s, int Ls, const double v[4]) {
+    pair_store<NT>(f4v{(float)v[0], (float)v[1], (float)v[2], (float)v[3]},
+                   reinterpret_cast<f4v*>(f) + row * Ls + s);
+  }
+};
+
+// row = 6 h + j and s of this lane's pair; false past the end
+__device__ __forceinline__ bool pair_of(const VecGeom& g, long long& row, int& s) {
+  const long long first = (long long)blockIdx.x * BS;
+  row = first / g.Ls;
+  const unsigned t = (unsigned)(first - row * g.Ls) + threadIdx.x;  // the division by lane in 32 bits
+  row += t / (unsigned)g.Ls;
+  s = (int)(t % (unsigned)g.Ls);
+  return row < 6 * g.V4h;
+}
+
+template <int P, bool NT>
+__global__ void __launch_bounds__(BS) cg_dir_pair_kernel(VecGeom g, const char* __restrict__ r,
+                                                         const char* __restrict__ p, char* __restrict__ pn, size_t sr,
+                                                         size_t sp, double* __restrict__ scal, int keep) {
+  const int rhs = blockIdx.y;
+  double* sc = scal + rhs * NSCAL;
+  if (blockIdx.x == 0 && threadIdx.x == 0) sc[keep] = sc[S_ALPHA];
+  long long row;
+  int s;
+  if (!pair_of(g, row, s)) return;
+  const double beta = sc[S_BETA];
+  double vr[4], vp[4];
+  PairOf<P, NT>::load(p + rhs * sp, row, s, g.Ls, vp);
+  PairOf<P, NT>::load(r + rhs * sr, row, s, g.Ls, vr);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) vr[c] = fma(beta, vp[c], vr[c]);
+  PairOf<P, NT>::store(pn + rhs * sp, row, s, g.Ls, vr);
+}
+
+template <int P, int N, bool NT>
+__global__ void __launch_bounds__(BS) cg_flush_pair_kernel(VecGeom g, char* x, DirSet d, const char* r, char* pn,
+                                                           size_t sx, size_t sp, const double* __restrict__ scal) {
+  const int rhs = blockIdx.y;
+  long long row;
+  int s;
+  if (!pair_of(g, row, s)) return;
+  const double* sc = scal + rhs * NSCAL;
+  double alpha[N];
+  bool any = false;
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    alpha[k] = sc[d.slot[k]];
+    any |= alpha[k] != 0.0;
+  }
+  double vp[N][4];
+#pragma unroll
+  for (int k = 0; k < N; ++k)
+    if (alpha[k] != 0.0 || (k == N - 1 && pn != nullptr)) PairOf<P, NT>::load(d.p[k] + rhs * sp, row, s, g.Ls, vp[k]);
+  if (any) {
+    double vx[4];
+    PairOf<DWF_F64, true>::load(x + rhs * sx, row, s, g.Ls, vx);
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+      if (alpha[k] != 0.0)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) vx[c] = fma(alpha[k], vp[k][c], vx[c]);
+    PairOf<DWF_F64, true>::store(x + rhs * sx, row, s, g.Ls, vx);
+  }
+  if (pn == nullptr) return;
+  const double beta = sc[S_BETA];
+  double vr[4];
+  PairOf<P, NT>::load(r + rhs * sp, row, s, g.Ls, vr);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) vr[c] = fma(beta, vp[N - 1][c], vr[c]);
+  PairOf<P, NT>::store(pn + rhs * sp, row, s, g.Ls, vr);
+}
+
 // p = r + beta p.  With orth (right after a reliable update replaced r by the
 // true residual), p first loses its component along the new r,
 // p <- p - (r^dag p / |r|^2) r, so that p = (1 - beta c) r + beta p with
@@ -446,6 +562,18 @@ __global__ void scal_beta_kernel(double* scal, int nrhs) {
   if (r < nrhs) beta_step(scal + r * NSCAL);
 }
 
+// total t of the per-site sums into its slot and the CG step that needs it
+__device__ __forceinline__ void finish_sum(double* s, double t, int slot, int mode, double tol2) {
+  s[slot] = t;
+  if (mode == 1) {
+    alpha_step(s);
+  } else if (mode >= 2) {
+    beta_step(s);
+    converge_step(s, tol2, 1, mode == 2);
+    if (mode == 3 && s[S_ACTIVE] != 0.0) s[S_RRMAX] = fmax(s[S_RRMAX], s[S_RR]);
+  }
+}
+
 // Per-site sums (one FP64 value per half-lattice site and rhs, at the site's
 // index) reduced into slot, then on the same thread the CG step that needs the
 // total: mode 0 none, 1 alpha (slot = S_PAP), 2 beta and the convergence step
@@ -495,15 +623,35 @@ __global__ void __launch_bounds__(BS) sum_sites_kernel(const double* __restrict_
   double t = 0;
   for (int i = 0; i < SITE_RED_BLOCKS; ++i) t += rs[i];
   __hip_atomic_store(counters + rhs, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  double* s = scal + (size_t)rhs * NSCAL;
-  s[slot] = t;
-  if (mode == 1) {
-    alpha_step(s);
-  } else if (mode >= 2) {
-    beta_step(s);
-    converge_step(s, tol2, 1, mode == 2);
-    if (mode == 3 && s[S_ACTIVE] != 0.0) s[S_RRMAX] = fmax(s[S_RRMAX], s[S_RR]);
+  finish_sum(scal + (size_t)rhs * NSCAL, t, slot, mode, tol2);
+}
+
+// The same for a half lattice of up to SITE_ONE_WG sites: one workgroup a rhs, without the second
+// level and its atomic (8^3 x 16: 5.3 -> 4.3 us, 12^3 x 24 with two rhs 6.1 -> 5.2 us; beyond, one
+// CU's loads take longer than the second level).  Lane t adds the sums t, t + 1024, ... in a
+// binary tree, then the workgroup: an order fixed by the lattice alone, as above.
+constexpr int SITE_ONE_WG = 32768;
+constexpr int SITE_LANES = 1024;
+
+__global__ void __launch_bounds__(SITE_LANES) sum_sites_small_kernel(const double* __restrict__ partials, int count,
+                                                                     double* __restrict__ scal, int slot, int mode,
+                                                                     double tol2) {
+  const int rhs = blockIdx.x;
+  const double* q = partials + (size_t)rhs * count;
+  double acc[SITE_ONE_WG / SITE_LANES];
+#pragma unroll
+  for (int j = 0; j < SITE_ONE_WG / SITE_LANES; ++j) {
+    const int k = j * SITE_LANES + (int)threadIdx.x;
+    acc[j] = k < count ? q[k] : 0.0;
   }
+#pragma unroll
+  for (int w = SITE_ONE_WG / SITE_LANES / 2; w > 0; w >>= 1)
+#pragma unroll
+    for (int j = 0; j < w; ++j) acc[j] += acc[j + w];
+  __shared__ double red[2 * (SITE_LANES / 64)];
+  double unused = 0;
+  block_sum2(acc[0], unused, red);
+  if (threadIdx.x == 0) finish_sum(scal + (size_t)rhs * NSCAL, acc[0], slot, mode, tol2);
 }
 
 __global__ void scal_set_kernel(double* scal, int nrhs, int slot, double v) {
@@ -586,7 +734,11 @@ hipError_t reduce_sites(dwf_context* ctx, const double* partials, int count, int
                         double tol2) {
   if ((size_t)nrhs * SITE_RED_BLOCKS > ctx->partial_count * RED_BLOCKS * 2 || nrhs > (int)ctx->partial_count)
     return hipErrorInvalidValue;
-  hipLaunchKernelGGL(sum_sites_kernel, dim3(SITE_RED_BLOCKS, nrhs), dim3(BS), 0, ctx->stream, partials, count,
+  if (count <= SITE_ONE_WG)
+    hipLaunchKernelGGL(sum_sites_small_kernel, dim3(nrhs), dim3(SITE_LANES), 0, ctx->stream, partials, count,
+                       ctx->scalars, slot, mode, tol2);
+  else
+    hipLaunchKernelGGL(sum_sites_kernel, dim3(SITE_RED_BLOCKS, nrhs), dim3(BS), 0, ctx->stream, partials, count,
                      ctx->partials, ctx->counters, ctx->scalars, slot, mode, tol2);
   return hipGetLastError();
 }
@@ -728,10 +880,24 @@ hipError_t cg_update_xp(dwf_context* ctx, int px, char* x, int pr, const char* r
   return hipGetLastError();
 }
 
+// Non-temporal accesses of r and p where a field of all rhs exceeds the 32 MiB that the XCDs' L2
+// hold together: the hop passes that follow then keep more of their neighbour data (FP64 CG
+// iteration on 16^3 x 32 -1.4 %).  A smaller field is found in L2 by the pass that reads it next
+// (8^3 x 16 Ls 12 action 37.3 -> 36.4 ms).
+static bool stream_past_l2(const dwf_context* ctx, int prec, int nrhs) {
+  return (double)field_bytes_rhs(ctx, prec) * nrhs > 32.0 * 1024 * 1024;
+}
+
 template <int PR, int PP>
 static void dir_l(dwf_context* ctx, VecGeom g, const char* r, const char* p, char* pn, int keep, int nrhs) {
-  hipLaunchKernelGGL((cg_dir_kernel<PR, PP>), dim3(grid_n(g.n), nrhs), dim3(BS), 0, ctx->stream, g, r, p, pn,
-                     field_bytes_rhs(ctx, PR), field_bytes_rhs(ctx, PP), ctx->scalars, keep);
+  if constexpr (PR == PP) {
+    auto k = stream_past_l2(ctx, PP, nrhs) ? cg_dir_pair_kernel<PP, true> : cg_dir_pair_kernel<PP, false>;
+    hipLaunchKernelGGL(k, dim3(grid_n(6 * g.n), nrhs), dim3(BS), 0, ctx->stream, g, r, p, pn, field_bytes_rhs(ctx, PR),
+                       field_bytes_rhs(ctx, PP), ctx->scalars, keep);
+  }
+  else
+    hipLaunchKernelGGL((cg_dir_kernel<PR, PP>), dim3(grid_n(g.n), nrhs), dim3(BS), 0, ctx->stream, g, r, p, pn,
+                       field_bytes_rhs(ctx, PR), field_bytes_rhs(ctx, PP), ctx->scalars, keep);
 }
 
 hipError_t cg_next_dir(dwf_context* ctx, int pr, const char* r, int pp, const char* p, char* pn, int keep, int nrhs) {
@@ -750,9 +916,15 @@ hipError_t cg_next_dir(dwf_context* ctx, int pr, const char* r, int pp, const ch
 
 template <int PR, int PP, int N>
 static void flush_n(dwf_context* ctx, VecGeom g, char* x, const DirSet& d, const char* r, char* pn, int nrhs) {
-  hipLaunchKernelGGL((cg_flush_kernel<PR, PP, N>), dim3(grid_n(g.n), nrhs), dim3(BS), 0, ctx->stream, g, x, d, r, pn,
-                     field_bytes_rhs(ctx, DWF_F64), field_bytes_rhs(ctx, PR), field_bytes_rhs(ctx, PP),
-                     ctx->scalars);
+  if constexpr (PR == PP) {
+    auto k = stream_past_l2(ctx, PP, nrhs) ? cg_flush_pair_kernel<PP, N, true> : cg_flush_pair_kernel<PP, N, false>;
+    hipLaunchKernelGGL(k, dim3(grid_n(6 * g.n), nrhs), dim3(BS), 0, ctx->stream, g, x, d, r, pn,
+                       field_bytes_rhs(ctx, DWF_F64), field_bytes_rhs(ctx, PP), ctx->scalars);
+  }
+  else
+    hipLaunchKernelGGL((cg_flush_kernel<PR, PP, N>), dim3(grid_n(g.n), nrhs), dim3(BS), 0, ctx->stream, g, x, d, r, pn,
+                       field_bytes_rhs(ctx, DWF_F64), field_bytes_rhs(ctx, PR), field_bytes_rhs(ctx, PP),
+                       ctx->scalars);
 }
 
 template <int PR, int PP>

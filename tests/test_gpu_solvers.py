@@ -47,6 +47,23 @@ def test_cg_f64_c1(nrhs):
         assert abs(iters[k] - ref.iterations) <= 3
 
 
+@pytest.mark.parametrize("prec", [F64, F32])
+@pytest.mark.parametrize("dims,Ls,nrhs", [((2, 2, 2, 2), 1, 2), ((4, 2, 2, 6), 5, 3), ((2, 4, 4, 6), 12, 1)])
+def test_cg_update_lanes_at_ragged_sizes(dims, Ls, nrhs, prec):
+    """The lane-per-pair updates of x and p and the one-workgroup sums where the last workgroup is
+    partly empty and Ls is no power of two: the returned x solves A x = b, to the bar above."""
+    op, U = make_operator(dims, Ls, eps=0.3, seed=51, prec=prec, max_nrhs=nrhs, max_cg_rhs=nrhs)
+    op64, _ = make_operator(dims, Ls, U=U)  # b and x are FP64 at either precision
+    b = even_fields(dims, Ls, nrhs, seed=52)
+    x = op.new_field(nrhs, prec=F64)
+    code, iters, res = op.cg(pack(op64, b, EVEN), x, nrhs, tol=1e-10, maxiter=5000)
+    xg = unpack(op64, x, nrhs, EVEN)
+    for k in range(nrhs):
+        true = np.linalg.norm((b[k] - oracle_A(U)(xg[k])).ravel()) / np.linalg.norm(b[k].ravel())
+        assert true < 1e-10 * 1.5
+        assert abs(true - res[k]) < 1e-11
+
+
 def test_cg_initial_guess_is_used():
     dims, Ls = C1
     op, U = make_operator(dims, Ls, seed=0)
