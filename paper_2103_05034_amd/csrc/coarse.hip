@@ -149,7 +149,7 @@ __global__ void __launch_bounds__(512) block_dot_kernel(BlockArgs a) {
       if (use) Store<P>::load(a.v + par[q] * a.v_ps + (size_t)(r0 + r) * a.stride, a.g.V4h, a.g.Ls, h[q], s[q], v[q][r]);
     }
   const int kend = a.nvec;
-  for (int k0 = 0; k0 < kend; k0 += KG) {
+  for (int k0 = blockIdx.z * KG; k0 < kend; k0 += KG * gridDim.z) {
     double acc[2 * RT * KG];
 #pragma unroll
     for (int i = 0; i < 2 * RT * KG; ++i) acc[i] = 0;
@@ -192,7 +192,111 @@ __global__ void __launch_bounds__(512) block_dot_kernel(BlockArgs a) {
   }
 }
 
-// INPLACE = false: out_r = sum_k coef[r][b][k] phi_k^b for the KT right-hand
+// Pair j of component pairs (2j, 2j + 1) at (h, s): 16 bytes of an FP32 field, twice 16 of an FP64 one.
+template <class R>
+__device__ __forceinline__ void load_pair(const char* f, long long row, int Ls, int s, cplx<R> v[2]) {
+  if constexpr (sizeof(R) == 8) {
+    const double2* q = reinterpret_cast<const double2*>(f) + 2 * row * Ls + s;
+    const double2 x = q[0], y = q[Ls];
+    v[0] = {x.x, x.y};
+    v[1] = {y.x, y.y};
+  } else {
+    const float4 x = reinterpret_cast<const float4*>(f)[row * Ls + s];
+    v[0] = {x.x, x.y};
+    v[1] = {x.z, x.w};
+  }
+}
+template <class R>
+__device__ __forceinline__ void store_pair(char* f, long long row, int Ls, int s, const cplx<R> v[2]) {
+  if constexpr (sizeof(R) == 8) {
+    double2* q = reinterpret_cast<double2*>(f) + 2 * row * Ls + s;
+    q[0] = make_double2(v[0].re, v[0].im);
+    q[Ls] = make_double2(v[1].re, v[1].im);
+  } else {
+    reinterpret_cast<float4*>(f)[row * Ls + s] = make_float4(v[0].re, v[0].im, v[1].re, v[1].im);
+  }
+}
+
+// out_r = sum_k coef[r][b][k] phi_k^b for the KT right-hand sides r = blockIdx.y * KT + ... of FP64
+// and FP32 fields; a lane holds NP of a spinor's six component pairs, 6 / NP workgroups a block.
+// Bound by the read of the basis.  8^3 x 16, Ls 8, 2^4 blocks of the even sites, 24 FP64 vectors:
+// 51 -> 24 us for one rhs, 56 -> 34 for eight; 16^3 x 32, Ls 16, 40 FP32 vectors: 750 us for one
+// (5.3 TB/s), 3290 -> 1850 for eight.
+template <class R, int KT, int NP>
+__global__ void __launch_bounds__(512) prolong_kernel(BlockArgs a) {
+  constexpr int U = NP == 1 ? 4 : 1;  // vectors in flight
+  extern __shared__ double cs[];      // complex coefficients [KT][nvec] of the block
+  const int b = blockIdx.x, first = blockIdx.z * NP;
+  const int np = a.nsb * a.g.Ls;
+  const int n = a.nvec;
+  const int r0 = blockIdx.y * KT;
+  for (int i = threadIdx.x; i < KT * n; i += blockDim.x) {
+    const int r = i / n, k = i - r * n;
+    double re = 0, im = 0;
+    if (r0 + r < a.nrhs) {
+      const double* c = a.coef + 2 * (((size_t)(r0 + r) * a.nb + b) * n + k);
+      re = c[0];
+      im = c[1];
+    }
+    cs[2 * i] = re;
+    cs[2 * i + 1] = im;
+  }
+  __syncthreads();
+  for (int p = threadIdx.x; p < np; p += blockDim.x) {
+    const int jsite = p / a.g.Ls;
+    const int s = p - jsite * a.g.Ls;
+    long long h = a.bsite[(size_t)b * a.nsb + jsite];
+    const int par = split_site(a.g.V4h, h);
+    const long long row = 6 * h + first;
+    const char* bb = a.basis + par * a.basis_ps;
+    cplx<double> acc[KT][2 * NP];
+#pragma unroll
+    for (int t = 0; t < KT; ++t)
+#pragma unroll
+      for (int c = 0; c < 2 * NP; ++c) acc[t][c] = {0, 0};
+    auto load = [&](int j, cplx<R> f[2 * NP]) {
+#pragma unroll
+      for (int k = 0; k < NP; ++k) load_pair<R>(bb + (size_t)j * a.stride, row + k, a.g.Ls, s, f + 2 * k);
+    };
+    auto add = [&](int j, const cplx<R> f[2 * NP]) {
+#pragma unroll
+      for (int t = 0; t < KT; ++t) {
+        const double cr = cs[2 * (t * n + j)], ci = cs[2 * (t * n + j) + 1];
+#pragma unroll
+        for (int c = 0; c < 2 * NP; ++c) {
+          acc[t][c].re = fma(cr, (double)f[c].re, fma(-ci, (double)f[c].im, acc[t][c].re));
+          acc[t][c].im = fma(cr, (double)f[c].im, fma(ci, (double)f[c].re, acc[t][c].im));
+        }
+      }
+    };
+    int j = 0;
+    for (; j + U <= n; j += U) {
+      cplx<R> f[U][2 * NP];
+#pragma unroll
+      for (int k = 0; k < U; ++k) load(j + k, f[k]);
+#pragma unroll
+      for (int k = 0; k < U; ++k) add(j + k, f[k]);
+    }
+    for (; j < n; ++j) {
+      cplx<R> f[2 * NP];
+      load(j, f);
+      add(j, f);
+    }
+    char* ob = a.out + par * a.out_ps;
+#pragma unroll
+    for (int t = 0; t < KT; ++t) {
+      if (r0 + t >= a.nrhs) continue;
+#pragma unroll
+      for (int k = 0; k < NP; ++k) {
+        const cplx<double>*v = acc[t] + 2 * k;
+        const cplx<R> o[2] = {{(R)v[0].re, (R)v[0].im}, {(R)v[1].re, (R)v[1].im}};
+        store_pair<R>(ob + (size_t)(r0 + t) * a.stride, row + k, a.g.Ls, s, o);
+      }
+    }
+  }
+}
+
+// FP16 + scale, whose stored form needs the spinor's largest number.  INPLACE = false: out_r = sum_k coef[r][b][k] phi_k^b for the KT right-hand
 //   sides r = blockIdx.y * KT + ...
 // INPLACE = true: phi_k <- sum_{j<=k} W[b][j][k] phi_j^b for every k, one
 //   workgroup per block taking the k tiles from the top down, so that the
@@ -371,17 +475,25 @@ template <int P, int RT, int PP>
 static void dot_t(const dwf_context* c, const BlockArgs& a) {
   const int lanes = group_of(lanes_of(c));
   const size_t lds = (size_t)(lanes / 64) * 2 * RT * KG * sizeof(double);
-  hipLaunchKernelGGL((block_dot_kernel<P, RT, PP>), dim3(a.nb, (a.nrhs + RT - 1) / RT), dim3(lanes), lds, c->stream,
-                     a);
+  // Up to a wave a SIMD (1024) the batches of basis vectors go to several workgroups, each with its
+  // own copy of v: 8^3 x 16, Ls 8, 24 FP64 vectors, one rhs 39 -> 25 us; with more waves the copies
+  // cost more than they hide (three rhs of 4 x 4 x 2 x 4 blocks, 1536 waves: 32 -> 39 us).
+  const long long waves = (long long)a.nb * ((a.nrhs + RT - 1) / RT) * (lanes / 64);
+  const int groups = (a.nvec + KG - 1) / KG;
+  const int split = waves <= 1024 ? (int)std::min<long long>(groups, 4096 / waves) : 1;
+  hipLaunchKernelGGL((block_dot_kernel<P, RT, PP>), dim3(a.nb, (a.nrhs + RT - 1) / RT, split), dim3(lanes), lds,
+                     c->stream, a);
 }
 
-// blocks of up to 512 5D sites: one site and two rhs per lane; up to 1024: two sites and one rhs
+// blocks of up to 512 5D sites: one site and one or two rhs per lane; up to 1024: two sites and one rhs
 template <int P>
 static void dot_p(const dwf_context* c, const BlockArgs& a) {
-  if (lanes_of(c) <= 512)
-    dot_t<P, 2, 1>(c, a);
-  else
+  if (lanes_of(c) > 512)
     dot_t<P, 1, 2>(c, a);
+  else if (a.nrhs == 1)
+    dot_t<P, 1, 1>(c, a);
+  else
+    dot_t<P, 2, 1>(c, a);
 }
 
 hipError_t launch_block_dot(dwf_context* c, int prec, const char* basis, int nvec, const char* v, int nrhs,
@@ -407,6 +519,30 @@ static void combine_t(const dwf_context* c, const BlockArgs& a) {
   hipLaunchKernelGGL((block_combine_kernel<P, KT, INPLACE>), dim3(a.nb, gy), dim3(lanes), lds, c->stream, a);
 }
 
+template <class R, int KT, int NP>
+static void prolong_t(const dwf_context* c, const BlockArgs& a) {
+  const size_t lds = (size_t)KT * a.nvec * 2 * sizeof(double);
+  hipLaunchKernelGGL((prolong_kernel<R, KT, NP>),
+                     dim3(a.nb, (unsigned)((a.nrhs + KT - 1) / KT), 6 / NP), dim3(group_of(lanes_of(c))),
+                     lds, c->stream, a);
+}
+
+template <class R>
+static void prolong_r(const dwf_context* c, const BlockArgs& a) {
+  // Up to four waves a CU a lane per spinor leaves the chip waiting on its chain of vectors, so a
+  // lane takes a sixth of one; for three or more rhs the small accumulators of that form also let
+  // four share a read of the basis.  Else the lane per spinor reads each site's lines together.
+  const bool whole = (long long)a.nb * (group_of(lanes_of(c)) / 64) >= 4096;
+  if (a.nrhs > 2)
+    prolong_t<R, 4, 1>(c, a);
+  else if (whole)
+    prolong_t<R, 2, 6>(c, a);
+  else if (a.nrhs == 2)
+    prolong_t<R, 2, 1>(c, a);
+  else
+    prolong_t<R, 1, 1>(c, a);
+}
+
 hipError_t launch_block_prolong(dwf_context* c, int prec, const char* basis, int nvec, const double* coef, int nrhs,
                                 char* out) {
   BlockArgs a = block_args(c, prec, basis, nvec);
@@ -415,8 +551,8 @@ hipError_t launch_block_prolong(dwf_context* c, int prec, const char* basis, int
   a.out = out;
   a.out_ps = c->coarse_both ? (size_t)nrhs * a.stride : 0;
   switch (prec) {
-    case DWF_F64: combine_t<DWF_F64, 2, false>(c, a); break;
-    case DWF_F32: combine_t<DWF_F32, 2, false>(c, a); break;
+    case DWF_F64: prolong_r<double>(c, a); break;
+    case DWF_F32: prolong_r<float>(c, a); break;
     default: combine_t<DWF_F16S, 2, false>(c, a); break;
   }
   return hipGetLastError();

@@ -81,6 +81,41 @@ def test_restrict_and_prolong(prec, block):
         assert relmax(got[r], C.prolong(list(B), cc[r], dims, block)) < tol
 
 
+@pytest.mark.parametrize("prec", [F64, F32, F16S])
+@pytest.mark.parametrize(
+    "dims, Ls, block, nvec, nrhs, both",
+    [
+        ((4, 4, 4, 4), 5, (2, 2, 2, 2), 1, 1, False),  # one vector, one rhs
+        ((4, 4, 4, 4), 8, (2, 2, 2, 2), 9, 1, True),  # three batches of vectors on workgroups of their own
+        ((4, 4, 4, 6), 7, (2, 2, 2, 2), 6, 2, True),  # no whole number of vectors in flight, two rhs
+        ((4, 4, 4, 4), 12, (4, 4, 4, 2), 8, 5, False),  # two sites a lane; a second tile of rhs with one
+        ((8, 8, 16, 32), 1, (2, 2, 2, 1), 3, 2, False),  # 4096 waves: a lane per spinor
+    ],
+)
+def test_restrict_and_prolong_shapes(prec, dims, Ls, block, nvec, nrhs, both):
+    import torch
+
+    parity = 2 if both else EVEN
+    op, _ = make_operator(dims, Ls, prec=prec, max_nrhs=2)
+    nb = op.set_blocks(block, both=both)
+
+    def held(n, seed):
+        raw = synth.gaussian_fermion_batch(dims, Ls, n, seed)
+        buf = pack(op, raw if both else L.on_parity(raw, EVEN), parity)
+        return buf, unpack(op, buf, n, parity)
+
+    basis, B = held(nvec, 53)
+    v, V = held(nrhs, 54)
+    c = coarse_host(op.restrict(basis, nvec, v, nrhs))
+    rng = np.random.default_rng(55)
+    cc = rng.standard_normal((nrhs, nb, nvec)) + 1j * rng.standard_normal((nrhs, nb, nvec))
+    got = unpack(op, op.prolong(basis, nvec, torch.from_numpy(cc).cuda(), nrhs), nrhs, parity)
+    tol = {F64: 1e-14, F32: 2e-7, F16S: 2e-3}[prec]
+    for r in range(nrhs):
+        assert relmax(c[r], C.restrict(list(B), V[r], dims, block)) < 1e-13
+        assert relmax(got[r], C.prolong(list(B), cc[r], dims, block)) < tol
+
+
 @pytest.mark.parametrize("block", [(2, 2, 2, 2), (4, 2, 4, 2)])
 def test_block_orthonormalize_f64(block):
     dims, Ls = C1
