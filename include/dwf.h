@@ -537,7 +537,8 @@ int dwf_tune_cache_clear(void);
  * times every n-th hop launch (a stride coprime with the launches of one
  * solver iteration -- four per CG iteration -- samples every kind evenly and
  * puts fewer event records between the kernels); every call resets the sums.
- * DWF_EINVAL for enable < 0.  dwf_kernel_time reports the summed duration
+ * DWF_EINVAL for enable < 0.  A D_DW over both parities (dwf_ddw, the HDCR
+ * calls) is one launch.  dwf_kernel_time reports the summed duration
  * (ms) and the number of timed launches since the last reset (it synchronises
  * the stream). */
 int dwf_enable_timing(dwf_handle h, int enable);
