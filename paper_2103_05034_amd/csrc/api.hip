@@ -49,8 +49,6 @@ static_assert(SPINOR_BYTES[DWF_F64] == Store<DWF_F64>::bytes_per_spinor &&
                   SPINOR_BYTES[DWF_F16S] == Store<DWF_F16S>::bytes_per_spinor,
               "the workspace plan and the kernels agree on the packed spinor sizes");
 
-size_t up(size_t n) { return (n + WS_ALIGN - 1) / WS_ALIGN * WS_ALIGN; }
-
 using plan::valid_dims;
 
 // Points the handle's buffers into its workspace by the host-side plan.
@@ -1302,7 +1300,7 @@ int dwf_chiral_split(dwf_handle h, const void* in, void* out, int nvec) {
 
 size_t dwf_block_scratch_bytes(dwf_handle h, int nvec) {
   if (!h || h->nb <= 0 || nvec < 1 || nvec > 64) return 0;
-  return 2 * up((size_t)h->nb * nvec * nvec * 16) + WS_ALIGN;
+  return plan::block_scratch(0, h->nb, nvec).bytes;
 }
 
 int dwf_block_orthonormalize(dwf_handle h, void* basis, int nvec, void* scratch, size_t scratch_bytes) {
@@ -1312,9 +1310,10 @@ int dwf_block_orthonormalize(dwf_handle h, void* basis, int nvec, void* scratch,
     return fail(DWF_ENOMEM, "dwf_block_orthonormalize: scratch of %zu bytes, %zu needed", scratch_bytes,
                 dwf_block_scratch_bytes(h, nvec));
   char* base = reinterpret_cast<char*>(scratch);
-  double* gram = reinterpret_cast<double*>(base);
-  double* w = reinterpret_cast<double*>(base + up((size_t)h->nb * nvec * nvec * 16));
-  int* flag = reinterpret_cast<int*>(base + 2 * up((size_t)h->nb * nvec * nvec * 16));
+  const plan::BlockScratch s = plan::block_scratch(reinterpret_cast<uintptr_t>(scratch), h->nb, nvec);
+  double* gram = reinterpret_cast<double*>(base + s.gram);
+  double* w = reinterpret_cast<double*>(base + s.w);
+  int* flag = reinterpret_cast<int*>(base + s.flag);
   char* q = reinterpret_cast<char*>(basis);
   HIP_TRY(hipMemsetAsync(flag, 0, sizeof(int), h->stream));
   for (int pass = 0; pass < 2; ++pass) {  // Cholesky QR, twice

@@ -19,6 +19,16 @@ namespace {
 size_t round_up(size_t n) { return (n + WS_ALIGN - 1) / WS_ALIGN * WS_ALIGN; }
 }  // namespace
 
+BlockScratch block_scratch(size_t base, int nb, int nvec) {
+  const size_t matrices = round_up((size_t)nb * nvec * nvec * 16);
+  BlockScratch s;
+  s.gram = (16 - base % 16) % 16;
+  s.w = s.gram + matrices;
+  s.flag = s.w + matrices;
+  s.bytes = 2 * matrices + WS_ALIGN;  // the last part holds the shift and the flag
+  return s;
+}
+
 bool valid_dims(const int dims[4], int Ls, int prec, int max_nrhs, int max_cg_rhs, std::string* why) {
   if (!dims) {
     *why = "dims is NULL";

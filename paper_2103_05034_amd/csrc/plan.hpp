@@ -109,6 +109,16 @@ constexpr int NUM_BOX_CANDIDATES = sizeof(BOX_CANDIDATES) / sizeof(BOX_CANDIDATE
 bool build_blocks(int X, int Y, int Z, int T, int Ls, const int block[4], bool both, std::vector<int>& sites,
                   std::vector<int>& nbrs, int* nblocks, int* sites_per_block, std::string* why);
 
+// Parts of the caller's scratch for the block orthonormalisation, as byte offsets from
+// `base`, which may be aligned to a double only: the kernels read and write the Gram
+// matrices and W in 16-byte units, so the parts start at the next multiple of 16.  `bytes`
+// is what the caller must bring, whatever the base.
+struct BlockScratch {
+  size_t gram, w, flag;  // [nb][nvec][nvec] complex128 each, one int
+  size_t bytes;
+};
+BlockScratch block_scratch(size_t base, int nb, int nvec);
+
 // Launch shapes found by the autotuner, kept per (GPU architecture, lattice,
 // Ls, rhs count, precision, traversal order or "tuned", occupancy cap, Schur form) for
 // the life of the process and, when a file path is given, in that file (one

@@ -403,8 +403,26 @@ static void check_cholesky() {
   CHECK(!plan::cholesky_upper(nan1, 1, R, 0.0), "cholesky accepted a NaN pivot");
 }
 
+// The parts of an orthonormalisation's scratch at every alignment a caller may bring.
+static void check_block_scratch() {
+  for (int nb : {1, 3, 16, 8192})
+    for (int nvec : {1, 7, 40, 64}) {
+      const size_t matrices = (size_t)nb * nvec * nvec * 16;
+      const size_t bytes = plan::block_scratch(0, nb, nvec).bytes;
+      for (size_t base = 4096; base < 4096 + 512; base += 4) {
+        const plan::BlockScratch s = plan::block_scratch(base, nb, nvec);
+        CHECK(s.bytes == bytes, "scratch size depends on the base");
+        CHECK((base + s.gram) % 16 == 0 && (base + s.w) % 16 == 0 && (base + s.flag) % 4 == 0,
+              "scratch parts misaligned (base %zu, nb %d, nvec %d)", base, nb, nvec);
+        CHECK(s.gram + matrices <= s.w && s.w + matrices <= s.flag && s.flag + sizeof(int) <= bytes,
+              "scratch parts overlap or overrun (base %zu, nb %d, nvec %d)", base, nb, nvec);
+      }
+    }
+}
+
 int main(int argc, char** argv) {
   check_valid_dims();
+  check_block_scratch();
   check_cholesky();
   check_tune_cache(argc > 1 ? argv[1] : ".");
   const int shapes[][4] = {{2, 2, 2, 2}, {4, 4, 6, 8}, {8, 4, 4, 8}, {16, 16, 16, 32}, {24, 24, 24, 48}, {6, 2, 10, 4}};

@@ -320,3 +320,26 @@ def test_gram_schmidt_ragged_sites(prec, unit, dims, Ls, nvec):
     for k in range(nvec):
         assert np.max(np.abs(Q[k] - Qo[k])) < tol * max(1.0, float(np.max(np.abs(Qo[k]))))
     assert np.max(np.abs(R - Ro)) < tol * np.max(np.abs(Ro))
+
+
+@pytest.mark.parametrize("offset", [4, 8, 24])
+def test_block_orthonormalize_scratch_alignment(offset):
+    """Scratch of exactly the stated size at a 4- or 8-byte boundary gives the bits of an aligned
+    one, and the bytes on both sides of it stay."""
+    import torch
+    import paper_2103_05034_amd as dwf
+
+    dims, Ls = C1
+    op, _ = make_operator(dims, Ls)
+    op.set_blocks((2, 2, 2, 2))
+    nvec = 9
+    want = pack(op, even_fields(dims, Ls, nvec, seed=56), EVEN)
+    got = want.clone()
+    op.block_orthonormalize(want, nvec)
+    nbytes = op.lib.dwf_block_scratch_bytes(op.h, nvec)
+    buf = torch.full((nbytes + 64,), 7, dtype=torch.uint8, device="cuda")
+    assert buf.data_ptr() % 64 == 0
+    dwf._check(op.lib.dwf_block_orthonormalize(op.h, got.data_ptr(), nvec, buf.data_ptr() + offset, nbytes))
+    torch.cuda.synchronize()
+    assert (got == want).all()
+    assert (buf[:offset] == 7).all() and (buf[offset + nbytes :] == 7).all()
