@@ -31,8 +31,10 @@ namespace dwf {
 namespace {
 
 typedef double d4v __attribute__((ext_vector_type(4)));
-typedef float f4v __attribute__((ext_vector_type(4)));
-typedef double d2v __attribute__((ext_vector_type(2)));
+// 16 bytes of a vector, which Gram-Schmidt takes at any multiple of 8 (as the combination's
+// accesses of one complex value do); the loads are global_load_dwordx4 all the same
+typedef float f4v __attribute__((ext_vector_type(4), aligned(8)));
+typedef double d2v __attribute__((ext_vector_type(2), aligned(8)));
 
 constexpr int GW = 4;  // waves of a workgroup
 

@@ -343,3 +343,24 @@ def test_block_orthonormalize_scratch_alignment(offset):
     torch.cuda.synchronize()
     assert (got == want).all()
     assert (buf[:offset] == 7).all() and (buf[offset + nbytes :] == 7).all()
+
+
+@pytest.mark.parametrize("prec", [F64, F32])
+@pytest.mark.parametrize("nvec", [3, 40, 64])
+def test_gram_schmidt_of_vectors_at_a_multiple_of_8(prec, nvec):
+    """Vectors aligned to 8 bytes only give the bits of aligned ones, and their surroundings stay."""
+    import torch
+
+    dims, Ls = (4, 4, 4, 6), 5
+    op, _ = make_operator(dims, Ls, prec=prec, max_nrhs=3)
+    want = pack(op, even_fields(dims, Ls, nvec, seed=57), EVEN)
+    n = want.numel()
+    buf = torch.full((n + 64,), 7, dtype=torch.uint8, device="cuda")
+    assert buf.data_ptr() % 64 == 0
+    got = buf[8 : n + 8]
+    got.copy_(want)
+    R = op.gram_schmidt(want, nvec)
+    assert np.array_equal(op.gram_schmidt(got, nvec), R)
+    torch.cuda.synchronize()
+    assert (got == want).all()
+    assert (buf[:8] == 7).all() and (buf[n + 8 :] == 7).all()
