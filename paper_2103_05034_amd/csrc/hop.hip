@@ -572,26 +572,11 @@ static size_t hop_lds(int prec, int spb, int Ls, int epi, bool reduce) {
   return (size_t)spb * 72 * cplx_bytes(prec) + scratch;
 }
 
-// Sites of a workgroup where the caller has chosen none, for a parity of `points` (site, s) pairs.
-// Up to 4 waves for each of the 1024 SIMDs every wave runs at once and the launch lasts as long as
-// its fullest CU: workgroups of one wave spread most evenly and none waits for another at a
-// barrier.  M_pc^dag M_pc with 64 against 256 lanes: FP64 4^4 Ls 8 31.5 and 36.9 us, 8^3 x 16
-// Ls 12 48.1 and 53.5, 12^3 x 24 Ls 10 151 and 172; FP32 27.2 and 29.0, 32.4 and 33.8, 76 and 84.
-// A wave that Ls does not fill to 7/8 gives that back (8^3 x 16 Ls 48: 148 and 145), so the
-// smallest workgroup that it does fill is taken (192 lanes: 138).  Above that size the wide
-// workgroup is as good or better (16^3 x 32 Ls 16 FP64 663 and 653, 24^3 x 48 Ls 12 3136 and 2992).
-static int default_tile(long long points, int Ls) {
-  int lanes = 256;
-  if (points <= 4 * 64 * 1024)
-    for (int l = 192; l >= 64; l -= 64)
-      if (l / Ls * Ls * 8 >= l * 7) lanes = l;
-  return std::min(lanes / Ls, 64);
-}
-
-void fill_shape(const dwf_context* ctx, HopArgs& a) {
+// `fields`: half fields that the launch goes over side by side
+void fill_shape(const dwf_context* ctx, HopArgs& a, int prec, bool site_local, long long fields) {
   const int Ls = ctx->g.Ls;
   int spb = ctx->spb;
-  if (spb <= 0) spb = default_tile(ctx->g.V4h * Ls, Ls);
+  if (spb <= 0) spb = plan::default_tile(prec, site_local, ctx->g.V4h * Ls, fields, Ls);
   if (spb * Ls > 256) spb = 256 / Ls;
   if (spb < 1) spb = 1;
   // every staging buffer must fit 64 KiB of LDS
@@ -674,6 +659,13 @@ static void parity_tables(const dwf_context* ctx, int prec, int out_parity, cons
   *order = ctx->order_mode ? ctx->order + (size_t)out_parity * V4h : nullptr;
 }
 
+// right-hand sides a workgroup takes one after another, and the groups they make
+static int rhs_per_block(const dwf_context* ctx, int nrhs) { return std::max(1, std::min(ctx->rpb, nrhs)); }
+static long long rhs_groups(const dwf_context* ctx, int nrhs) {
+  const int rpb = rhs_per_block(ctx, nrhs);
+  return (nrhs + rpb - 1) / rpb;
+}
+
 static hipError_t launch_filled(dwf_context* ctx, int prec, int pin, int px, HopArgs& a, int dag, int epi, int nrhs) {
   a.stride = field_bytes_rhs(ctx, prec);
   a.in_stride = field_bytes_rhs(ctx, pin);
@@ -681,7 +673,7 @@ static hipError_t launch_filled(dwf_context* ctx, int prec, int pin, int px, Hop
   a.lds_floor = ctx->lds_floor;
   a.one = 1.0f;
   a.nrhs = nrhs;
-  a.rpb = std::max(1, std::min(ctx->rpb, nrhs));
+  a.rpb = rhs_per_block(ctx, nrhs);
   const int depth = ctx->depth[pin];
   timing_begin(ctx);
   hipError_t e;
@@ -701,7 +693,7 @@ static hipError_t launch_filled(dwf_context* ctx, int prec, int pin, int px, Hop
 hipError_t launch_hop_ex(dwf_context* ctx, int prec, int pin, int px, HopArgs a, int out_parity, int dag, int epi,
                          int nrhs) {
   if (prec != DWF_F64 && ctx->links32 == nullptr) return hipErrorInvalidValue;  // FP64 handles hold no FP32 links
-  fill_shape(ctx, a);
+  fill_shape(ctx, a, prec, false, rhs_groups(ctx, nrhs));
   parity_tables(ctx, prec, out_parity, &a.links, &a.nbr, &a.order);
   return launch_filled(ctx, prec, pin, px, a, dag, epi, nrhs);
 }
@@ -719,7 +711,7 @@ hipError_t launch_hop_ex(dwf_context* ctx, int prec, int pin, int px, HopArgs a,
 // fastest; neither is behind the two launches at any size measured.
 hipError_t launch_hop_both(dwf_context* ctx, int prec, HopArgs even, const HopArgs& odd, int dag, int epi, int nrhs) {
   if (prec != DWF_F64 && ctx->links32 == nullptr) return hipErrorInvalidValue;
-  fill_shape(ctx, even);
+  fill_shape(ctx, even, prec, false, 2 * rhs_groups(ctx, nrhs));
   even.both = prec == DWF_F64 ? HOP_SLOWEST : HOP_FASTEST;
   if (even.both == HOP_FASTEST) even.nb8 = (2 * even.nblocks + 7) / 8;
   parity_tables(ctx, prec, DWF_EVEN, &even.links, &even.nbr, &even.order);
@@ -753,7 +745,7 @@ static hipError_t launch_site5_p(const HopArgs& a, int dag, int inv, int nrhs, h
 
 hipError_t launch_site5(dwf_context* ctx, int prec, const char* in, char* out, int dag, int inv, int nrhs) {
   HopArgs a{};
-  fill_shape(ctx, a);
+  fill_shape(ctx, a, prec, true, nrhs);
   a.in = in;
   a.out = out;
   a.stride = field_bytes_rhs(ctx, prec);

@@ -26,7 +26,7 @@ void timing_begin(dwf_context* ctx);
 void timing_end(dwf_context* ctx);
 
 // hop.hip
-void fill_shape(const dwf_context* ctx, HopArgs& a);
+void fill_shape(const dwf_context* ctx, HopArgs& a, int prec, bool site_local, long long fields);
 hipError_t launch_hop(dwf_context* ctx, int prec, HopArgs a, int out_parity, int dag, int epi, int nrhs);
 // the same with the neighbour input stored at pin and the operand x at px (output at prec); the
 // mixed forms offered are FP16S in -> FP32 out (EPI_M5INV, no x) and FP32 in + FP16S x -> FP32

@@ -19,6 +19,35 @@ namespace {
 size_t round_up(size_t n) { return (n + WS_ALIGN - 1) / WS_ALIGN * WS_ALIGN; }
 }  // namespace
 
+// While every wave of a launch runs at once, it lasts as long as its fullest CU: workgroups of
+// one wave spread most evenly and none waits for another at a barrier.  M_pc^dag M_pc of one
+// field with 64 against 256 lanes: FP64 4^4 Ls 8 31.5 and 36.9 us, 8^3 x 16 Ls 12 47 and 53,
+// 12^3 x 24 Ls 10 151 and 172; FP32 27 and 29, 32 and 34, 77 and 84 (the other way at 12^4
+// Ls 16: FP64 126 and 121, FP32 60 and 58).  A wave that Ls does not fill to 7/8 gives that back
+// (8^3 x 16 Ls 48: 148 and 145), so the smallest workgroup that it does fill is taken (192 lanes:
+// 138).  A field of more than 4 waves for each of the 1024 SIMDs takes the wide workgroup, which
+// is as good or better there (16^3 x 32 Ls 16 FP64 663 and 653, 24^3 x 48 Ls 12 3136 and 2992).
+//
+// Several fields in a launch fill the chip in turn, and in FP64 and FP32 sharing neighbours
+// inside a wide workgroup then counts for more: at 12^3 x 24 Ls 10 D_hop of four FP64 fields
+// takes 123 us narrow and 112 wide, of eight 258 and 242; M^dag M of forty FP32 fields at
+// 8^3 x 16 Ls 12 565 and 543, D_DW of eight 57 and 49; up to twice the points of the line above
+// narrow is still ahead (M^dag M of two FP64 fields at 12^3 x 24 288 and 303, of eight FP32 ones
+// at 8^3 x 16 Ls 16 145 and 151).  FP16 + scale hops move half the bytes per lane and stay ahead
+// narrow with any number of fields (8^3 x 16 Ls 12: forty 383 and 430, D_hop 77 and 91), their
+// site-local M5D^{-1} does not (12^3 x 24: two fields 16.4 and 15.7, eight 46 and 43).
+int default_tile(int prec, bool site_local, long long points, long long fields, int Ls) {
+  constexpr long long FULL = 4 * 64 * 1024;
+  const bool narrow = points <= FULL && (prec != DWF_F16S ? points * fields <= 2 * FULL
+                                         : !site_local || points * fields <= FULL);
+  int lanes = 256;
+  if (narrow)
+    for (int l = 192; l >= 64; l -= 64)
+      if (l / Ls * Ls * 8 >= l * 7) lanes = l;
+  const int sites = lanes / Ls;
+  return sites < 64 ? sites : 64;
+}
+
 BlockScratch block_scratch(size_t base, int nb, int nvec) {
   const size_t matrices = round_up((size_t)nb * nvec * nvec * 16);
   BlockScratch s;

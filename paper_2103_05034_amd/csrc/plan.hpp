@@ -109,6 +109,11 @@ constexpr int NUM_BOX_CANDIDATES = sizeof(BOX_CANDIDATES) / sizeof(BOX_CANDIDATE
 bool build_blocks(int X, int Y, int Z, int T, int Ls, const int block[4], bool both, std::vector<int>& sites,
                   std::vector<int>& nbrs, int* nblocks, int* sites_per_block, std::string* why);
 
+// Sites of a workgroup of the hop and M5D kernels where the caller has chosen none: `points`
+// (site, s) pairs of a half field, `fields` half fields side by side in the launch (groups of
+// right-hand sides, times two for a D_DW over both parities).
+int default_tile(int prec, bool site_local, long long points, long long fields, int Ls);
+
 // Parts of the caller's scratch for the block orthonormalisation, as byte offsets from
 // `base`, which may be aligned to a double only: the kernels read and write the Gram
 // matrices and W in 16-byte units, so the parts start at the next multiple of 16.  `bytes`

@@ -420,8 +420,35 @@ static void check_block_scratch() {
     }
 }
 
+// The default workgroup on both sides of every line of its rule.
+static void check_default_tile() {
+  const auto tile = plan::default_tile;
+  for (int prec = 0; prec < 3; ++prec)
+    for (int Ls = 1; Ls <= 128; ++Ls)
+      for (long long points : {16LL * Ls, 1LL << 18, (1LL << 18) + 1, 1LL << 30})
+        for (long long fields : {1LL, 2LL, 8192LL}) {
+          const int n = tile(prec, false, points, fields, Ls), w = 256 / Ls < 64 ? 256 / Ls : 64;
+          CHECK(n >= 1 && n <= w && n * Ls <= 256, "tile %d of Ls %d", n, Ls);
+          if (points > 1 << 18) CHECK(n == w, "a large field has a narrow tile");
+        }
+  const long long p = 8 * 8 * 8 * 16 / 2 * 12;  // 49152 points
+  for (int prec : {DWF_F64, DWF_F32})
+    for (bool site_local : {false, true}) {
+      CHECK(tile(prec, site_local, p, 1, 12) == 5, "one field: a wave");
+      CHECK(tile(prec, site_local, p, 10, 12) == 5, "ten fields: a wave");
+      CHECK(tile(prec, site_local, p, 11, 12) == 21, "eleven fields: four waves");
+      CHECK(tile(prec, site_local, p, 40, 12) == 21, "forty fields: four waves");
+    }
+  CHECK(tile(DWF_F16S, false, p, 40, 12) == 5, "FP16 hop of forty fields: a wave");
+  CHECK(tile(DWF_F16S, true, p, 5, 12) == 5, "FP16 M5D of five fields: a wave");
+  CHECK(tile(DWF_F16S, true, p, 6, 12) == 21, "FP16 M5D of six fields: four waves");
+  CHECK(tile(DWF_F64, false, 1 << 18, 2, 16) == 4 && tile(DWF_F64, false, 1 << 18, 3, 16) == 16, "twice the line");
+  CHECK(tile(DWF_F64, false, 4096 * 48, 1, 48) == 4, "Ls 48: three waves");
+}
+
 int main(int argc, char** argv) {
   check_valid_dims();
+  check_default_tile();
   check_block_scratch();
   check_cholesky();
   check_tune_cache(argc > 1 ? argv[1] : ".");

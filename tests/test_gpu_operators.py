@@ -162,6 +162,28 @@ def test_default_tile_matches_widest(Ls, prec):
     assert all((a == b).all() for a, b in zip(*got))
 
 
+@pytest.mark.parametrize("prec", [F64, F32, F16S])
+@pytest.mark.parametrize("dims,Ls,nrhs,rpb", [((8, 8, 8, 8), 16, 9, 1), ((8, 8, 8, 8), 16, 9, 4), ((4, 4, 4, 4), 12, 342, 1)])
+def test_default_tile_of_many_right_hand_sides(dims, Ls, nrhs, rpb, prec):
+    """Past the number of fields where the default workgroup changes (524288 points in a launch,
+    262144 for the FP16 + scale M5D; with rhs looped over inside a workgroup, fewer side by side)
+    it gives bitwise the fields of one wave and of the widest, which the parity tests above pin."""
+    op, _ = make_operator(dims, Ls, eps=0.5, seed=53, prec=prec, max_nrhs=nrhs)
+    inp = pack(op, fields(dims, Ls, 3, seed=54), BOTH).view(2, 3, -1)
+    both = inp[:, [k % 3 for k in range(nrhs)]].contiguous()
+    even, both = both[0].contiguous().view(-1), both.view(-1)
+    got = []
+    for spb in (0, 64 // Ls, 256 // Ls):
+        op.set_tile(spb, 0, rpb)
+        pc, m5, full = op.new_field(nrhs), op.new_field(nrhs), op.new_field(nrhs, both=True)
+        op.mpcdagmpc(even, pc, nrhs)
+        op.m5d_inv(even, m5, nrhs)
+        op.ddw(both, full, nrhs)
+        got.append((pc, m5, full))
+    for other in got[1:]:
+        assert all((a == b).all() for a, b in zip(got[0], other))
+
+
 @pytest.mark.parametrize("dims,Ls", SHAPES)
 def test_mpc_and_normal_operator_f64(dims, Ls):
     nrhs = 2
