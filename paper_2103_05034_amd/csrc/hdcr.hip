@@ -180,25 +180,27 @@ struct MatvecTail {
 
 // y[b] = sum_r A[b][r] x[neighbour_r(b)]: one workgroup per block.  A block's
 // stencil is 9 n rows of n contiguous entries, entry j of row (r, k) times x_k of
-// neighbour r adding to y_j; MVT / n rows go through the workgroup at a time, so
-// nearly every lane streams, eight rows in flight, and the lanes' sums for one j are
-// added in order through LDS.  The nine input vectors pass through LDS.  512 blocks
-// of 24 vectors in complex128 (42 MB): 31 -> 19 us against one lane per j and one row
-// at a time, which left 40 of a wave's 64 lanes idle; 8192 blocks of 32 (1.21 GB):
-// 184 us both ways (6.6 TB/s), in complex64 125 -> 93 us.  128 lanes: 256 took 188 us
-// and 64 took 191 us there.
+// neighbour r adding to y_j.  The nine input vectors pass through LDS.  Two forms
+// (matvec_t takes one by size):
+// * LANES = MVT: MVT / n rows go through the workgroup at a time, so nearly every lane
+//   streams, eight rows in flight, and the lanes' sums for one j are added in order
+//   through LDS.  512 blocks of 24 vectors in complex128 (42 MB, from the caches): 30 -> 9 us
+//   back to back against the other form, which leaves 40 of a wave's 64 lanes idle;
+//   8192 blocks of 32 (1.21 GB): 184 us both ways (6.6 TB/s), in complex64 126 -> 93 us.
+//   128 lanes: 256 took 188 us and 64 took 191 us there.
+// * LANES = 64: a wave per block, one lane per j and one row at a time.
 constexpr int MVT = 128;
-template <class T, int MODE>
-__global__ void __launch_bounds__(MVT) coarse_matvec_kernel(const T* __restrict__ A, const int* __restrict__ bnbr,
-                                                           int n, const double2* __restrict__ x, double2* __restrict__ y,
-                                                           MatvecTail tail) {
+template <class T, int MODE, int LANES>
+__global__ void __launch_bounds__(LANES)
+coarse_matvec_kernel(const T* __restrict__ A, const int* __restrict__ bnbr, int n, const double2* __restrict__ x,
+                     double2* __restrict__ y, MatvecTail tail) {
   typedef typename std::conditional<sizeof(T) == 16, double, float>::type E;
   typedef E ev __attribute__((ext_vector_type(2)));
   constexpr int U = 8;  // rows in flight per lane
   __shared__ double2 xs[9 * 64];
-  __shared__ double2 sums[MVT];
+  __shared__ double2 sums[LANES > 64 ? LANES : 1];
   const int b = blockIdx.x;
-  const int G = MVT / n;  // rows at a time
+  const int G = LANES > 64 ? LANES / n : 1;  // rows at a time
   const int g = threadIdx.x / n, j = threadIdx.x - g * n;
   const int rows = g < G ? 9 * n : 0;  // the lanes left over have none
   const T* Ab = A + (size_t)b * 9 * n * n + j;
@@ -210,8 +212,8 @@ __global__ void __launch_bounds__(MVT) coarse_matvec_kernel(const T* __restrict_
       m[u] = i < rows ? __builtin_nontemporal_load(reinterpret_cast<const ev*>(Ab + (size_t)i * n)) : ev{0, 0};
     }
   };
-  fetch(g);  // before the inputs: it needs none of them
-  for (int i = threadIdx.x; i < 9 * n; i += MVT) {
+  if (LANES > 64) fetch(g);  // before the inputs: it needs none of them
+  for (int i = threadIdx.x; i < 9 * n; i += LANES) {
     const int r = i / n, k = i - r * n;
     const int src = r < 8 ? bnbr[(size_t)b * 8 + r] : b;
     xs[i] = x[(size_t)src * n + k];
@@ -229,25 +231,33 @@ __global__ void __launch_bounds__(MVT) coarse_matvec_kernel(const T* __restrict_
   }
   __syncthreads();
   double re = 0, im = 0;
-  for (int i0 = g; i0 < rows; i0 += U * G) {
-    ev w[U];
+  auto add = [&](ev w, double2 v) {
+    re = fma((double)w.x, v.x, fma(-(double)w.y, v.y, re));
+    im = fma((double)w.x, v.y, fma((double)w.y, v.x, im));
+  };
+  if constexpr (LANES > 64) {
+    for (int i0 = g; i0 < rows; i0 += U * G) {
+      ev w[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) w[u] = m[u];
-    if (i0 + U * G < rows) fetch(i0 + U * G);
+      for (int u = 0; u < U; ++u) w[u] = m[u];
+      if (i0 + U * G < rows) fetch(i0 + U * G);
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int i = i0 + u * G;
-      if (i >= rows) break;
-      const double2 v = xs[i];
-      re = fma((double)w[u].x, v.x, fma(-(double)w[u].y, v.y, re));
-      im = fma((double)w[u].x, v.y, fma((double)w[u].y, v.x, im));
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + u * G;
+        if (i >= rows) break;
+        add(w[u], xs[i]);
+      }
     }
+    sums[threadIdx.x] = make_double2(re, im);
+    __syncthreads();
+  } else if (g == 0) {
+    for (int r = 0; r < 9; ++r)
+      for (int k = 0; k < n; ++k)
+        add(__builtin_nontemporal_load(reinterpret_cast<const ev*>(Ab + ((size_t)r * n + k) * n)), xs[r * n + k]);
   }
-  sums[threadIdx.x] = make_double2(re, im);
-  __syncthreads();
   double norm = 0, unused = 0;
   if ((int)threadIdx.x < n) {
-    double2 o = sums[threadIdx.x];
+    double2 o = make_double2(re, im);  // the first row's lanes
     for (int k = 1; k < G; ++k) {
       o.x += sums[threadIdx.x + k * n].x;
       o.y += sums[threadIdx.x + k * n].y;
@@ -265,7 +275,7 @@ __global__ void __launch_bounds__(MVT) coarse_matvec_kernel(const T* __restrict_
     norm = fma(o.x, o.x, o.y * o.y);
   }
   if (MODE != MV_PLAIN) {
-    __shared__ double red[2 * ((MVT + 63) / 64)];
+    __shared__ double red[2 * (LANES / 64)];
     block_sum2(norm, unused, red);
     if (threadIdx.x == 0) tail.part_out[b] = norm;
   }
@@ -500,15 +510,32 @@ int smoother(dwf_hdcr_s* hd, const char* r, char* out) {
   return DWF_OK;
 }
 
+template <class T, int MODE, int LANES>
+hipError_t matvec_l(dwf_hdcr_s* hd, const double2* x, double2* y, const MatvecTail& tail) {
+  hipLaunchKernelGGL((coarse_matvec_kernel<T, MODE, LANES>), dim3(hd->nb), dim3(LANES), 0, hd->h->stream,
+                     reinterpret_cast<const T*>(hd->A), hd->h->bnbr, hd->nvec, x, y, tail);
+  return hipGetLastError();
+}
+
+// A stencil that no cache holds is bound by HBM, and there the wave per block, with fewer lines
+// asked for at a time and none shared by two waves, streams better once it leaves few lanes idle.
+// 8192 blocks, one wave against MVT lanes: complex128 of 33, 43 and 64 vectors 206 and 210, 343 and
+// 368, 723 and 719 us, complex64 of 43, 50 and 60 203 and 216, 246 and 266, 321 and 348 (complex64 of
+// 33 to 42 stays ahead on MVT lanes, 116 against 139 at 33).  Fewer blocks do not fill the chip with a
+// wave each: complex128 of 43 meets at about 2200 (2048 blocks 91 and 90 us, 2304 100 and 107, 3072 123
+// and 141), complex64, whose loads are half as long, at about 3000 (2560 of 60 110 and 112, of 43 83 and
+// 71; 3072 of 60 121 and 130, of 43 86 and 80).
+template <class T, int MODE>
+hipError_t matvec_t(dwf_hdcr_s* hd, const double2* x, double2* y, const MatvecTail& tail) {
+  const bool wide = sizeof(T) == 16;
+  const bool one_wave = wide ? hd->nb > 2048 && hd->nvec > 32 : hd->nb >= 3072 && hd->nvec > MVT / 3;
+  return one_wave ? matvec_l<T, MODE, 64>(hd, x, y, tail) : matvec_l<T, MODE, MVT>(hd, x, y, tail);
+}
+
 template <int MODE>
 hipError_t coarse_matvec(dwf_hdcr_s* hd, const double2* x, double2* y, const MatvecTail& tail) {
-  if (hd->prm.coarse_prec == DWF_F32)
-    hipLaunchKernelGGL((coarse_matvec_kernel<float2, MODE>), dim3(hd->nb), dim3(MVT), 0, hd->h->stream,
-                       reinterpret_cast<const float2*>(hd->A), hd->h->bnbr, hd->nvec, x, y, tail);
-  else
-    hipLaunchKernelGGL((coarse_matvec_kernel<double2, MODE>), dim3(hd->nb), dim3(MVT), 0, hd->h->stream,
-                       reinterpret_cast<const double2*>(hd->A), hd->h->bnbr, hd->nvec, x, y, tail);
-  return hipGetLastError();
+  return hd->prm.coarse_prec == DWF_F32 ? matvec_t<float2, MODE>(hd, x, y, tail)
+                                        : matvec_t<double2, MODE>(hd, x, y, tail);
 }
 
 // c = A^{-1} d by CG on A^2 c = A d from c = 0; stops when |A d - A^2 c| <= tol |A d|.

@@ -445,3 +445,39 @@ def test_coarse_matvec_and_cg_shapes(dims, Ls, nvec, prec):
         p, rr = r + new / rr * p, new
     assert it == 20
     assert np.linalg.norm(host(c) - want) < 20 * 1e4 * 2.0**-53 * 9 * nvec * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("T, nvec, prec", [(18, 33, 0), (24, 43, 1)])
+def test_coarse_matvec_and_cg_one_wave_per_block(T, nvec, prec):
+    """The fewest vectors whose matvec gives a block one wave instead of two, in either storage of
+    the stencil (beyond 2048 blocks in complex128, from 3072 on in complex64)."""
+    test_coarse_matvec_and_cg_shapes((8, 16, 16, T), 1, nvec, prec)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_coarse_matvec_one_wave_of_64_vectors(prec):
+    import paper_2103_05034_amd as dwf
+
+    dims, block, n = (8, 16, 16, 24), (2, 2, 2, 2), 64
+    op, _ = make_operator(dims, 1, prec=F64, max_nrhs=1, max_cg_rhs=2)
+    nb = op.set_blocks(block, both=True)
+    hd = dwf.HDCR(op, n, nkrylov=1, coarse_prec=prec)
+    hd.set_basis(pack(op, synth.gaussian_fermion_batch(dims, 1, n, 54), BOTH))
+    S = host(hd.coarse_operator())  # [nb, 9, k, j]
+    coords, ng = block_coords(dims, block)
+    rng = np.random.default_rng(55)
+    x = rng.standard_normal((nb, n)) + 1j * rng.standard_normal((nb, n))
+    got = host(hd.coarse_apply(dev_tensor(x)))
+    for b in range(0, nb, 17):
+        c = coords[b]
+        src = []
+        for d in range(8):
+            cc = list(c)
+            cc[d // 2] = (cc[d // 2] + (ng[d // 2] - 1 if d % 2 else 1)) % ng[d // 2]
+            src.append(block_index(cc, ng))
+        xb = x[src + [b]]
+        A = S[b].astype(np.complex128)
+        want = np.einsum("dkj,dk->j", A, xb)
+        # 9 n complex products, each sum rounding at most 2 * 9 n times
+        bound = 4 * 9 * n * 2.0**-53 * np.einsum("dkj,dk->j", np.abs(A), np.abs(xb))
+        assert np.all(np.abs(got[b] - want) <= bound)
