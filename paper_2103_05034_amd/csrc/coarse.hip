@@ -529,11 +529,16 @@ static void prolong_t(const dwf_context* c, const BlockArgs& a) {
 
 template <class R>
 static void prolong_r(const dwf_context* c, const BlockArgs& a) {
-  // Up to four waves a CU a lane per spinor leaves the chip waiting on its chain of vectors, so a
+  // Below four waves a SIMD a lane per spinor leaves the chip waiting on its chain of vectors, so a
   // lane takes a sixth of one; for three or more rhs the small accumulators of that form also let
   // four share a read of the basis.  Else the lane per spinor reads each site's lines together.
+  // Up to three FP32 vectors that also holds for three and more rhs: the outputs are then most of
+  // the bytes, and six workgroups a block write them in pieces (16^3 x 32, 2^4 blocks, four rhs: one
+  // vector 98 us whole and 130 in sixths at Ls 16, 74 and 137 at Ls 12, three vectors 182 and 157,
+  // 137 and 170; four vectors 220 and 165, 167 and 163; FP64 of one 228 and 200, 177 and 159).
   const bool whole = (long long)a.nb * (group_of(lanes_of(c)) / 64) >= 4096;
-  if (a.nrhs > 2)
+  const bool few = sizeof(R) == 4 && a.nvec <= 3;
+  if (a.nrhs > 2 && !(whole && few))
     prolong_t<R, 4, 1>(c, a);
   else if (whole)
     prolong_t<R, 2, 6>(c, a);

@@ -364,3 +364,11 @@ def test_gram_schmidt_of_vectors_at_a_multiple_of_8(prec, nvec):
     torch.cuda.synchronize()
     assert (got == want).all()
     assert (buf[:8] == 7).all() and (buf[n + 8 :] == 7).all()
+
+
+@pytest.mark.parametrize("prec", [F64, F32])
+@pytest.mark.parametrize("nvec, nrhs", [(1, 3), (3, 5), (4, 3)])
+def test_prolong_of_few_vectors_to_several_right_hand_sides(prec, nvec, nrhs):
+    """Both sides of the number of vectors up to which three and more FP32 outputs are formed a
+    lane per spinor, two at a time, on a lattice of 4096 waves."""
+    test_restrict_and_prolong_shapes(prec, (8, 8, 16, 32), 1, (2, 2, 2, 1), nvec, nrhs, False)
