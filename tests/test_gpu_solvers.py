@@ -318,6 +318,42 @@ def test_cg_independent_of_launch_shape(prec):
                 assert torch.equal(x, ref[2]), (order, spb, depth, rpb)
 
 
+@pytest.mark.parametrize("prec", [F64, F32, F16S])
+@pytest.mark.parametrize(
+    "dims, nrhs",
+    [
+        ((16, 16, 16, 16), 2),  # 32768 sites a parity, the most that one workgroup adds
+        ((18, 14, 14, 22), 3),  # 38808: 64 ranges of 607 sites, the last one shorter
+        ((16, 16, 16, 18), 2),  # 36864: ranges of 576, no whole number of 256 lanes
+    ],
+)
+def test_cg_of_several_rhs_at_the_two_level_sums(dims, nrhs, prec):
+    """Both sides of the lattice size from where CG's per-site sums go over 64 workgroups and a last
+    one that finishes: the solves reach the residual by the oracle's operator and are bitwise the
+    same for two launch shapes, several right-hand sides at once."""
+    import torch
+
+    Ls = 2
+    op, U = make_operator(dims, Ls, seed=0, prec=prec, max_nrhs=nrhs, max_cg_rhs=nrhs, mf=0.1)
+    op64, _ = make_operator(dims, Ls, U=U, mf=0.1)
+    b = even_fields(dims, Ls, nrhs, seed=58)
+    b_dev = pack(op64, b, EVEN)
+    got = []
+    for spb, depth in ((5, 2), (64, 3)):
+        op.set_tile(spb, depth, 1)
+        x = op.new_field(nrhs, prec=F64)
+        code, iters, res = op.cg(b_dev, x, nrhs, tol=1e-10, maxiter=20000)
+        torch.cuda.synchronize()
+        assert code == 0 and max(res) < 1.5e-10
+        got.append((iters, res, x))
+    assert got[0][0] == got[1][0] and got[0][1] == got[1][1] and torch.equal(got[0][2], got[1][2])
+    xg = unpack(op64, got[0][2], nrhs, EVEN)
+    for k in range(nrhs):
+        true = np.linalg.norm((b[k] - L.mpcdagmpc(U, xg[k], M5, 0.1)).ravel()) / np.linalg.norm(b[k].ravel())
+        assert true < 1e-10 * 1.5
+        assert abs(true - got[0][1][k]) < 1e-11
+
+
 @pytest.mark.parametrize("nrhs", [1, 2])
 def test_cg_fixed_iteration_counts(nrhs):
     """CG stopped after 1..9 iterations (the FP64 solver adds its search
