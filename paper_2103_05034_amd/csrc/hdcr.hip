@@ -121,7 +121,7 @@ __global__ void __launch_bounds__(CB) caxpby_kernel(long long n, const double2* 
 // vector updates.  The scalars are kept twice: an iteration's last launch reads
 // one set and its first workgroup writes the other.
 // ---------------------------------------------------------------------------
-enum CgSlot { CS_RR = 0, CS_QQ, CS_ALPHA, CS_STOP, CS_ACTIVE, CS_ITERS, CS_GO, CS_BETA, CS_FLAG, CS_N = 16 };
+enum CgSlot { CS_RR = 0, CS_ALPHA, CS_STOP, CS_ACTIVE, CS_ITERS, CS_GO, CS_FLAG, CS_N = 16 };
 
 // Sum of np partial sums, in every thread of the workgroup (one fixed order).
 // Contains two barriers.
