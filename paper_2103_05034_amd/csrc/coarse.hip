@@ -14,14 +14,16 @@
 //   operator is coarsened (Deflation basis setup section).
 // * block_dot: c[r][b][k] = <phi_k^b, v_r>, the restrictor applied to nrhs
 //   fields.
-// * block_combine: out_r = sum_k c[r][b][k] phi_k^b (prolongator), or the
-//   in-place map phi_k <- sum_{j<=k} W[b][j][k] phi_j^b used to
-//   orthonormalise FP16 + scale fields (W = R^{-1} of the block's Cholesky
-//   factor); the other precisions and the Gram matrices are in gram.hip.
+// * prolong: out_r = sum_k c[r][b][k] phi_k^b, FP64 and FP32 fields.
+// * block_combine: the same for FP16 + scale fields, and the in-place map
+//   phi_k <- sum_{j<=k} W[b][j][k] phi_j^b that orthonormalises them
+//   (W = R^{-1} of the block's Cholesky factor); that map for the other
+//   precisions and the Gram matrices are in gram.hip.
 // * block_cholesky: per block G = R^dag R, then W = R^{-1}.
 //
 // One workgroup owns one block; its lane p = j * Ls + s holds one 5D site of
-// the block (blocks of more than 512 5D sites: lane p also holds site p + 512).  Spinor loads are contiguous along s as in every other kernel.
+// the block (blocks of more than 512 5D sites: lane p also holds site
+// p + 512).  Spinor loads are contiguous along s as in every other kernel.
 // Sums over a block are reduced in a fixed order (wavefront shuffles, then
 // the waves in index order), so results are reproducible run to run.
 #include <algorithm>
@@ -296,15 +298,16 @@ __global__ void __launch_bounds__(512) prolong_kernel(BlockArgs a) {
   }
 }
 
-// FP16 + scale, whose stored form needs the spinor's largest number.  INPLACE = false: out_r = sum_k coef[r][b][k] phi_k^b for the KT right-hand
+// FP16 + scale: a lane owns whole spinors, whose largest number it needs for the stored form (the
+// matrix-core combination and the lane-per-pair prolongation spread a spinor over lanes).
+// INPLACE = false: out_r = sum_k coef[r][b][k] phi_k^b for the KT right-hand
 //   sides r = blockIdx.y * KT + ...
 // INPLACE = true: phi_k <- sum_{j<=k} W[b][j][k] phi_j^b for every k, one
 //   workgroup per block taking the k tiles from the top down, so that the
 //   phi_j a tile still needs (j below the tile) are not yet overwritten; every
 //   lane reads and writes only its own 5D site.
-template <int P, int KT, bool INPLACE>
+template <int KT, bool INPLACE>
 __global__ void __launch_bounds__(512) block_combine_kernel(BlockArgs a) {
-  using R = typename Store<P>::real;
   extern __shared__ double cs[];  // complex coefficients of the workgroup
   const int b = blockIdx.x;
   const int np = a.nsb * a.g.Ls;
@@ -347,8 +350,8 @@ __global__ void __launch_bounds__(512) block_combine_kernel(BlockArgs a) {
 #pragma unroll
         for (int c = 0; c < 12; ++c) acc[t][c] = {0, 0};
       for (int j = 0; j < jmax; ++j) {
-        cplx<R> f[12];
-        Store<P>::load(bb + (size_t)j * a.stride, a.g.V4h, a.g.Ls, h, s, f);
+        cplx<float> f[12];
+        Store<DWF_F16S>::load(bb + (size_t)j * a.stride, a.g.V4h, a.g.Ls, h, s, f);
 #pragma unroll
         for (int t = 0; t < KT; ++t) {
           // coefficient of phi_j in output t
@@ -366,10 +369,10 @@ __global__ void __launch_bounds__(512) block_combine_kernel(BlockArgs a) {
       for (int t = 0; t < KT; ++t) {
         const int k = INPLACE ? k0 + t : blockIdx.y * KT + t;
         if (k >= (INPLACE ? n : a.nrhs)) continue;
-        cplx<R> o[12];
+        cplx<float> o[12];
 #pragma unroll
-        for (int c = 0; c < 12; ++c) o[c] = {(R)acc[t][c].re, (R)acc[t][c].im};
-        Store<P>::store(ob + (size_t)k * a.stride, a.g.V4h, a.g.Ls, h, s, o);
+        for (int c = 0; c < 12; ++c) o[c] = {(float)acc[t][c].re, (float)acc[t][c].im};
+        Store<DWF_F16S>::store(ob + (size_t)k * a.stride, a.g.V4h, a.g.Ls, h, s, o);
       }
     }
   }
@@ -511,12 +514,12 @@ hipError_t launch_block_dot(dwf_context* c, int prec, const char* basis, int nve
   return hipGetLastError();
 }
 
-template <int P, int KT, bool INPLACE>
+template <int KT, bool INPLACE>
 static void combine_t(const dwf_context* c, const BlockArgs& a) {
   const int lanes = group_of(lanes_of(c));
   const size_t lds = (INPLACE ? (size_t)a.nvec * a.nvec : (size_t)KT * a.nvec) * 2 * sizeof(double);
   const unsigned gy = INPLACE ? 1 : (unsigned)((a.nrhs + KT - 1) / KT);
-  hipLaunchKernelGGL((block_combine_kernel<P, KT, INPLACE>), dim3(a.nb, gy), dim3(lanes), lds, c->stream, a);
+  hipLaunchKernelGGL((block_combine_kernel<KT, INPLACE>), dim3(a.nb, gy), dim3(lanes), lds, c->stream, a);
 }
 
 template <class R, int KT, int NP>
@@ -558,7 +561,7 @@ hipError_t launch_block_prolong(dwf_context* c, int prec, const char* basis, int
   switch (prec) {
     case DWF_F64: prolong_r<double>(c, a); break;
     case DWF_F32: prolong_r<float>(c, a); break;
-    default: combine_t<DWF_F16S, 2, false>(c, a); break;
+    default: combine_t<2, false>(c, a); break;
   }
   return hipGetLastError();
 }
@@ -569,7 +572,7 @@ hipError_t launch_block_apply(dwf_context* c, int prec, char* basis, int nvec, c
   a.wmat = wmat;
   a.out = basis;
   a.out_ps = a.basis_ps;
-  combine_t<DWF_F16S, 2, true>(c, a);
+  combine_t<2, true>(c, a);
   return hipGetLastError();
 }
 
