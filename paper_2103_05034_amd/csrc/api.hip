@@ -1133,7 +1133,10 @@ static int gs_cholqr2(dwf_handle h, char* Q, int n, std::vector<double>& Rout) {
   const size_t cap = fbytes(h, P) * (size_t)h->partial_count;
   const size_t per = nn * 2 * sizeof(double);
   if (cap < 2 * per) return GS_USE_CGS2;
-  // ranges of the lattice, one per workgroup: two for every CU, four sites (one a wave) at least
+  // ranges of the lattice, one per workgroup: two for every CU, which is what the registers of five
+  // tiles allow (33 to 40 vectors), and four sites (one a wave) at least.  Fewer tiles leave room for
+  // more workgroups, but two are well ahead of the passes they replaced: 16^3 x 24 Ls 16, 3, 8 and 16
+  // FP32 vectors 191, 267 and 411 us (LDS Gram passes with up to 2048 ranges 1750, 1760 and 2040)
   long long nwg = (long long)(cap / per) - 1;
   nwg = std::min<long long>({nwg, 512, (h->g.V4h + 3) / 4});
   if (nwg < 1) return GS_USE_CGS2;

@@ -3,8 +3,8 @@
 // solve), FP64.
 //
 // * H_DW = Gamma_5 D_DW, (Gamma_5 v)_s = gamma_5 v_{Ls-1-s} (Spectrum of domain
-//   wall fermions section).  D_DW is the two-launch hop pass of dwf_ddw; the
-//   Gamma_5 is folded into a combine kernel.
+//   wall fermions section).  D_DW is the hop pass of dwf_ddw, one launch over
+//   both parities; the Gamma_5 is folded into a combine kernel.
 // * Little Dirac operator A^{ab}_{jk} = <phi_j^a | H_DW | phi_k^b> (Two level
 //   preconditioner section).  It couples a block to itself and to its eight
 //   neighbours only, and is stored as that 9-point stencil, [nb][9][n][n]

@@ -22,9 +22,12 @@
 //
 // What bounds it: the fabric, then the matrix cores.  16^3 x 32, Ls 16, 32 vectors on
 // 2^4 blocks takes 21.5 ms: 0.62 TFLOP (36 complex inner steps per 5D site, 9 ms at the
-// 69 TFLOP/s the FP64 matrix cores reach) and 108 GB of line reads at 5.0 TB/s -- own
-// vectors once, neighbours four times, the site-local part twice; a block's 1.6 MB of
-// vectors do not stay in an L2 that 32 workgroups share.  Measured before: a workgroup
+// 69 TFLOP/s the FP64 matrix cores reach) and 108 GB of line reads by the L1s, 100 GB of
+// them from beyond L2, with 8.4 GB written where the stencil is 1.2 GB, together 5.0 TB/s --
+// own vectors once, neighbours four times, the site-local part twice (it could come from the
+// staged vectors); a block's 1.6 MB of vectors do not stay in an L2 that 32 workgroups share.
+// The two-tile forms spill 58 registers (228 bytes a lane), the three-tile form 81 (328), part
+// of them in the site loop: scratch traffic and the waits for it are in these figures.  Measured before: a workgroup
 // per stencil point and block with both operands loaded 64 bytes of a line at a time,
 // 41.9 ms (285 GB, 6.3 TB/s); nine fields written per basis vector and each restricted
 // onto the whole basis, 389 ms.
@@ -342,8 +345,13 @@ hipError_t launch_s(dwf_context* c, const StencilArgs& a, E* A) {
   return hipGetLastError();
 }
 
-// Row tiles per group: as many as the registers of two waves per SIMD hold (three); 49 to
-// 64 vectors take two groups of two.  LDS: 56, 117, 112 and 116 KB of a CU's 160 at
+// Row tiles per group: up to three, which the registers of two waves per SIMD hold but for the
+// spills above; 49 to 64 vectors take two groups of two.  A tile is 16 x 16 whatever the number of
+// vectors, so the time hardly falls below 16 of them: 16^4, Ls 8, 1, 2, 8 and 16 vectors 1.05, 1.04,
+// 1.20 and 1.79 ms.  A field per stencil point and restrictions were ahead for one vector (0.55 ms;
+// two 1.28, eight 9.2), and for up to three on a lattice of a few blocks, where a block's chain of
+// sites is all there is (4^4, Ls 8: one 41 against 93 us, four 120 against 96); a chirality-split
+// basis holds two at least, and the call comes once per basis.  LDS: 56, 117, 112 and 116 KB of a CU's 160 at
 // n = 16, 32, 48 and 64.
 template <class E>
 hipError_t launch_t(dwf_context* c, const StencilArgs& a, E* A) {
