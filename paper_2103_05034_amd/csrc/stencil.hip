@@ -337,6 +337,131 @@ stencil_kernel(StencilArgs a, const double2* __restrict__ links, const int* __re
   }
 }
 
+// The same for N = 1 or 2 vectors, whose products would leave a 16 x 16 tile all but empty: on the
+// vector units, a lane per (site, s) of the block, bound by the loads' latency at the one or two
+// waves a SIMD that its registers allow.  16^4, Ls 8, 2^4 blocks: one vector 102 us against 1.05 ms in
+// a tile (and 0.54 ms with a field per stencil point, each restricted), two 0.52 against 1.03 (1.28);
+// 4^4, where a block's chain of sites is all there is, 26 against 93 us (40) and 43 against 94 (65).
+constexpr int FEW = 256;  // lanes
+
+template <int N, class E>
+__global__ void __launch_bounds__(FEW)
+stencil_few_kernel(StencilArgs a, const double2* __restrict__ links, const int* __restrict__ bsite,
+                   const int* __restrict__ nbr, E* __restrict__ A) {
+  constexpr int NN = N * N, SUMS = 5 * NN;  // per (j, k): the four forward faces, the block itself
+  __shared__ double2 red[FEW / 64][SUMS];
+  const int b = (blockIdx.x & 7) * a.nb8 + (blockIdx.x >> 3);
+  if (b >= a.nb) return;  // whole workgroup leaves together
+  const int Ls = a.g.Ls;
+  const long long V4h = a.g.V4h;
+  const int ext[4] = {a.g.X, a.g.Y, a.g.Z, a.g.T};
+  cplx<double> acc[SUMS];  // [point][j][k]
+#pragma unroll
+  for (int i = 0; i < SUMS; ++i) acc[i] = {0, 0};
+  auto add = [](cplx<double> x, cplx<double> y, cplx<double>& s) {  // s += conj(x) y
+    s.re = fma(x.re, y.re, fma(x.im, y.im, s.re));
+    s.im = fma(x.re, y.im, fma(-x.im, y.re, s.im));
+  };
+  for (int p = threadIdx.x; p < a.nsb * Ls; p += FEW) {
+    const int i = p / Ls, s = p - i * Ls, sr = Ls - 1 - s;
+    const long long e = bsite[(size_t)b * a.nsb + i];
+    const int par = e >= V4h ? 1 : 0;
+    const long long h = e - par * V4h;
+    auto field = [&](int q, int k, long long site) {
+      return reinterpret_cast<const double2*>(a.basis + ((size_t)q * N + k) * a.fb) + site * 12 * Ls;
+    };
+    double2 own[N][12];
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+#pragma unroll
+      for (int c = 0; c < 12; ++c) own[j][c] = field(par, j, h)[c * Ls + s];
+    // the forward hops from the mirrored slice, across a face or inside
+    int along = 1;
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) {
+      const Direction dir(mu);
+      const bool face = a.blk[mu] != ext[mu] && i / along % a.blk[mu] == a.blk[mu] - 1;
+      along *= a.blk[mu];
+      const long long nh = nbr[((size_t)par * 8 + 2 * mu) * V4h + h];
+      const double2* lk = links + ((size_t)(par * 8 + 2 * mu) * 9) * V4h + h;
+      double2 u[9];
+#pragma unroll
+      for (int c = 0; c < 9; ++c) u[c] = lk[c * V4h];
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        const double2* f = field(1 - par, k, nh);
+#pragma unroll
+        for (int sp = 0; sp < 2; ++sp) {
+          cplx<double> hs[3];
+#pragma unroll
+          for (int c = 0; c < 3; ++c) hs[c] = dir.half<-1>(sp, f[(3 * sp + c) * Ls + sr], f[(dir.lo[sp] + c) * Ls + sr]);
+#pragma unroll
+          for (int r = 0; r < 3; ++r) {
+            cplx<double> chi = cmul(cplx<double>{u[3 * r].x, u[3 * r].y}, hs[0]);
+            chi = cfma(cplx<double>{u[3 * r + 1].x, u[3 * r + 1].y}, hs[1], chi);
+            chi = cfma(cplx<double>{u[3 * r + 2].x, u[3 * r + 2].y}, hs[2], chi);
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+              const cplx<double> x = dir.half<+1>(sp, own[j][3 * sp + r], own[j][dir.lo[sp] + r]);
+              if (face)
+                add(x, chi, acc[mu * NN + j * N + k]);
+              else
+                add(x, chi, acc[4 * NN + j * N + k]);
+            }
+          }
+        }
+      }
+    }
+    // the site-local part at the mirrored slice, with the signs of stencil_kernel
+#pragma unroll
+    for (int c = 0; c < 12; ++c) {
+      const bool upper = c < 6;
+      const int s1 = upper ? (sr > 0 ? sr - 1 : Ls - 1) : (sr + 1 < Ls ? sr + 1 : 0);
+      const bool wrap = upper ? sr == 0 : sr + 1 == Ls;
+      const double sg = upper ? -1.0 : 1.0, c0 = sg * a.d, c1 = wrap ? sg * a.mf : -sg;
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        const double2 v0 = field(par, k, h)[c * Ls + sr], v1 = field(par, k, h)[c * Ls + s1];
+        const cplx<double> m = {c0 * v0.x + c1 * v1.x, c0 * v0.y + c1 * v1.y};
+#pragma unroll
+        for (int j = 0; j < N; ++j) add(cplx<double>{own[j][c].x, own[j][c].y}, m, acc[4 * NN + j * N + k]);
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < SUMS; ++i) {
+    const double re = wave_sum(acc[i].re), im = wave_sum(acc[i].im);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][i] = make_double2(re, im);
+  }
+  __syncthreads();
+  if ((int)threadIdx.x >= SUMS) return;
+  auto total = [&](int i) {  // the waves in order, times -1/2
+    double2 t = red[0][i];
+    for (int w = 1; w < FEW / 64; ++w) {
+      t.x += red[w][i].x;
+      t.y += red[w][i].y;
+    }
+    return make_double2(-0.5 * t.x, -0.5 * t.y);
+  };
+  const int point = threadIdx.x / NN, j = threadIdx.x % NN / N, k = threadIdx.x % N;
+  const double2 t = total(threadIdx.x);
+  E* Ab = A + (size_t)b * 9 * NN;
+  if (point < 4) {
+    put(Ab + 2 * point * NN + k * N + j, t.x, t.y);
+    put(A + ((size_t)a.bnbr[(size_t)b * 8 + 2 * point] * 9 + 2 * point + 1) * NN + j * N + k, t.x, -t.y);
+  } else {
+    const double2 y = total(4 * NN + k * N + j);
+    put(Ab + 8 * NN + k * N + j, t.x + y.x, t.y - y.y);
+  }
+}
+
+template <int N, class E>
+hipError_t launch_few(dwf_context* c, const StencilArgs& a, E* A) {
+  hipLaunchKernelGGL((stencil_few_kernel<N, E>), dim3((unsigned)a.nb8 * 8), dim3(FEW), 0, c->stream, a,
+                     reinterpret_cast<const double2*>(c->links64), c->bsite, c->nbr, A);
+  return hipGetLastError();
+}
+
 template <int JT, int KW, int NBUF, class E>
 hipError_t launch_s(dwf_context* c, const StencilArgs& a, E* A) {
   const size_t lds = ((size_t)a.n * a.n + (size_t)NBUF * 12 * SL * (16 * JT + 1)) * sizeof(double2);
@@ -347,14 +472,13 @@ hipError_t launch_s(dwf_context* c, const StencilArgs& a, E* A) {
 
 // Row tiles per group: up to three, which the registers of two waves per SIMD hold but for the
 // spills above; 49 to 64 vectors take two groups of two.  A tile is 16 x 16 whatever the number of
-// vectors, so the time hardly falls below 16 of them: 16^4, Ls 8, 1, 2, 8 and 16 vectors 1.05, 1.04,
-// 1.20 and 1.79 ms.  A field per stencil point and restrictions were ahead for one vector (0.55 ms;
-// two 1.28, eight 9.2), and for up to three on a lattice of a few blocks, where a block's chain of
-// sites is all there is (4^4, Ls 8: one 41 against 93 us, four 120 against 96); a chirality-split
-// basis holds two at least, and the call comes once per basis.  LDS: 56, 117, 112 and 116 KB of a CU's 160 at
+// vectors, so the time hardly falls below 16 of them (16^4, Ls 8, 4, 8 and 16 vectors 1.15, 1.20
+// and 1.80 ms), and one and two vectors take the vector units.  LDS: 56, 117, 112 and 116 KB of a CU's 160 at
 // n = 16, 32, 48 and 64.
 template <class E>
 hipError_t launch_t(dwf_context* c, const StencilArgs& a, E* A) {
+  if (a.n == 1) return launch_few<1>(c, a, A);
+  if (a.n == 2) return launch_few<2>(c, a, A);
   switch ((a.n + 15) / 16) {
     case 1: return launch_s<1, 1, 2>(c, a, A);
     case 2: return launch_s<2, 2, 2>(c, a, A);

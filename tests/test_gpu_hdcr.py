@@ -481,3 +481,18 @@ def test_coarse_matvec_one_wave_of_64_vectors(prec):
         # 9 n complex products, each sum rounding at most 2 * 9 n times
         bound = 4 * 9 * n * 2.0**-53 * np.einsum("dkj,dk->j", np.abs(A), np.abs(xb))
         assert np.all(np.abs(got[b] - want) <= bound)
+
+
+@pytest.mark.parametrize(
+    "dims, Ls, block, nvec",
+    [
+        ((4, 4, 4, 8), 5, (2, 2, 2, 4), 1),  # 160 (site, s) of a block, no whole number of waves
+        ((4, 8, 4, 4), 3, (4, 2, 2, 2), 2),  # one block along x: no faces there; the waves past the block are idle
+        ((4, 4, 2, 4), 6, (2, 2, 1, 2), 2),  # blocks one site thick
+        ((4, 4, 4, 2), 1, (2, 2, 2, 2), 1),  # Ls 1, one block along t
+        ((4, 4, 4, 4), 16, (4, 2, 4, 2), 2),  # 1024 (site, s): four rounds of the lanes
+    ],
+)
+def test_stencil_of_one_and_two_vectors(dims, Ls, block, nvec):
+    """The vector-unit form for one or two vectors, to the same bar."""
+    test_stencil_shapes_match_oracle(dims, Ls, block, nvec)
