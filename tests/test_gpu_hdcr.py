@@ -394,10 +394,10 @@ def test_stencil_shapes_match_oracle(dims, Ls, block, nvec):
 @pytest.mark.parametrize(
     "dims, Ls, nvec, prec",
     [
-        ((4, 4, 4, 4), 2, 1, 0),  # more rows at a time (256) than a block has (9)
-        ((4, 4, 4, 8), 2, 3, 1),  # 27 rows, 85 at a time
-        ((4, 4, 4, 4), 4, 37, 0),  # six rows at a time, 34 lanes left over
-        ((4, 4, 4, 4), 4, 64, 1),  # four rows at a time, the most there are
+        ((4, 4, 4, 4), 2, 1, 0),  # more rows at a time (128) than a block has (9)
+        ((4, 4, 4, 8), 2, 3, 1),  # 27 rows, 42 at a time
+        ((4, 4, 4, 4), 4, 37, 0),  # three rows at a time, 17 lanes left over
+        ((4, 4, 4, 4), 4, 64, 1),  # two rows at a time, the fewest; the most vectors
         ((16, 16, 16, 16), 2, 2, 0),  # 4096 blocks: the norms' partial sums are reduced by ranges first
     ],
 )
