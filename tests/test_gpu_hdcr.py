@@ -359,7 +359,7 @@ def test_fullsize_algorithm_b_stencil_on_patches():
 @pytest.mark.parametrize(
     "dims, Ls, block, nvec",
     [
-        ((4, 4, 4, 4), 4, (2, 2, 2, 2), 1),  # one vector in a tile of 16
+        ((4, 4, 4, 4), 4, (2, 2, 2, 2), 1),  # one vector
         ((4, 4, 4, 8), 5, (2, 2, 2, 4), 16),  # a full tile; Ls no multiple of the 4 slices of a step
         ((4, 8, 4, 4), 3, (4, 2, 2, 2), 17),  # one vector into the second tile; one block along x: no faces there
         ((4, 4, 2, 4), 6, (2, 2, 1, 2), 33),  # third tile; blocks one site thick
@@ -481,6 +481,10 @@ def test_coarse_matvec_one_wave_of_64_vectors(prec):
         # 9 n complex products, each sum rounding at most 2 * 9 n times
         bound = 4 * 9 * n * 2.0**-53 * np.einsum("dkj,dk->j", np.abs(A), np.abs(xb))
         assert np.all(np.abs(got[b] - want) <= bound)
+
+
+def test_stencil_of_the_fewest_vectors_in_a_tile():
+    test_stencil_shapes_match_oracle((4, 4, 4, 4), 4, (2, 2, 2, 2), 3)
 
 
 @pytest.mark.parametrize(
