@@ -144,6 +144,21 @@ def test_ddw_both_parities_in_one_launch(dims, Ls, spb, prec, tol):
         assert rel_per_rhs(unpack(op, out, nrhs, BOTH), exp) < tol
 
 
+@pytest.mark.parametrize("prec,tol", [(F64, 1e-13), (F32, 1e-6), (F16S, 2e-3)])
+@pytest.mark.parametrize("rpb", [2, 3, 64])
+def test_ddw_both_parities_with_rhs_looped_over(rpb, prec, tol):
+    """The two-parity launch where a workgroup takes several right-hand sides, the last group short."""
+    dims, Ls, nrhs = (4, 4, 6, 8), 5, 5
+    op, U = make_operator(dims, Ls, eps=0.5, seed=55, prec=prec, max_nrhs=nrhs)
+    op.set_tile(7, 2, rpb)
+    inp = pack(op, fields(dims, Ls, nrhs, seed=56), BOTH)
+    src = unpack(op, inp, nrhs, BOTH)
+    out = op.new_field(nrhs, both=True)
+    op.ddw(inp, out, nrhs, True)
+    exp = np.stack([L.ddw(U, v, M5, MF, dag=True) for v in src])
+    assert rel_per_rhs(unpack(op, out, nrhs, BOTH), exp) < tol
+
+
 @pytest.mark.parametrize("prec", [F64, F32, F16S])
 @pytest.mark.parametrize("Ls", [1, 5, 24, 33, 48, 64, 96])
 def test_default_tile_matches_widest(Ls, prec):
